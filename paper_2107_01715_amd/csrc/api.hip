@@ -1995,26 +1995,45 @@ void mlp_enqueue(bcts_ctx* c, const MlpPlan& p, int n, int d, const float* state
   const bool corr_on = corr.enabled && d >= 1;
   const float gamma_d = (float)std::pow((double)gamma, d);
   long long cnt = n;
-  for (int k = 1; k <= d; ++k) {
-    cnt *= A;
-    if (k <= k0) continue;             // expanded on the host
+  k0 = std::max(k0, 0);                         // levels 1..k0 were expanded on the host (-1 at depth 0: none)
+  for (int k = 1; k <= k0; ++k) cnt *= A;
+  for (int k = k0 + 1; k <= d;) {
+    // As many levels in one launch as one workgroup's 16 children hold, while
+    // the launch's sub-trees (one per node of level k - 1) number at most
+    // twice the CUs: the chain of levels is then latency-bound, and a launch
+    // costs about as much as a level.
+    int m = 1;
+    for (long long last = A; m < 4 && k + m <= d && last * A <= 16 && cnt <= 512; ++m) last *= A;
     const float* ps = k == 1 ? states : F(p.states[k - 1]);
     const float* pret = k == 1 ? nullptr : F(p.ret[k - 1]);
-    float* os = k < d ? F(p.states[k]) : nullptr;
-    float* oret = (k < d || k == 1) ? F(p.ret[k]) : nullptr;
+    const int kl = k + m - 1;
+    float* os = kl < d ? F(p.states[kl]) : nullptr;
+    float* oret = (kl < d || kl == 1) ? F(p.ret[kl]) : nullptr;
     float* ov = (k == 1 && corr_on) ? F(p.v1) : nullptr;
-    float* oleaf = k == d ? F(p.leaf) : nullptr;
-    launch_mlp_level(c->mlp, cnt, ps, pret, (float)std::pow((double)gamma, k - 1), os, oret, ov, oleaf, gamma_d, s);
+    float* oleaf = kl == d ? F(p.leaf) : nullptr;
+    float gpow[4];
+    for (int i = 0; i < m; ++i) gpow[i] = (float)std::pow((double)gamma, k + i - 1);
+    cnt *= A;
+    if (m == 1)
+      launch_mlp_level(c->mlp, cnt, ps, pret, gpow[0], os, oret, ov, oleaf, gamma_d, s);
+    else
+      launch_mlp_levels(c->mlp, cnt, m, ps, pret, gpow, os, oret, k == 1 ? F(p.ret[1]) : nullptr, ov, oleaf, gamma_d, s);
+    for (int i = 1; i < m; ++i) cnt *= A;
+    k += m;
   }
-  if (d >= 1) launch_mlp_blockmax((long long)n * A, cnt / ((long long)n * A), F(p.leaf), F(p.qd), s);
+  // the leaf blocks' maxima: in the root kernel while a root's leaves are few
+  // for one workgroup, else a workgroup per block
+  const long long block = d >= 1 ? cnt / ((long long)n * A) : 0;
+  const bool in_root = d >= 1 && block * A <= 8192;
+  if (d >= 1 && !in_root) launch_mlp_blockmax((long long)n * A, block, F(p.leaf), F(p.qd), s);
   double pe = 0.0, po = 0.0;
   if (corr_on) {
     if (corr.mode == BCTS_CORR_EXACT_GEV) gev_coeffs(A, d, &pe, &po);
     else eq6_coeffs(A, d, &pe, &po);
   }
   launch_mlp_root(c->mlp, n, d, states, d >= 1 ? F(p.ret[1]) : nullptr, corr_on ? F(p.v1) : nullptr,
-                  d >= 1 ? F(p.qd) : nullptr, gamma, gamma_d, (float)pe, (float)po, corr_on ? 1 : 0,
-                  corr.enabled ? corr.scale : 0.f, act, q, s);
+                  in_root ? F(p.leaf) : nullptr, block, d >= 1 ? F(p.qd) : nullptr, gamma, gamma_d, (float)pe,
+                  (float)po, corr_on ? 1 : 0, corr.enabled ? corr.scale : 0.f, act, q, s);
 }
 }  // namespace
 
@@ -2028,9 +2047,9 @@ bcts_status bcts_set_mlp(bcts_ctx* c, int32_t A, const float* blob, size_t n_flo
   for (size_t i = 0; i < n_floats; ++i)
     if (!std::isfinite(blob[i])) return fail(c, BCTS_E_INVAL, "blob[%zu] is not finite", i);
   HIPCHECK(c, hipSetDevice(c->device));
-  // device order: w1s [100][100], w1a [A][100], b1, w2, b2, w3, b3, wo [101][100], bo, wq [A][100], bq
+  // host order: w1s [100][100], w1a [A][100], b1, w2 [100][100], b2, w3, b3, wo [101][100], bo, wq [A][100], bq
   const float* l1w = blob;
-  const float* rest = blob + (size_t)100 * (100 + A);   // l1.b onwards, already in device order after w1a
+  const float* rest = blob + (size_t)100 * (100 + A);   // l1.b onwards, already in this order after w1a
   std::vector<float> h;
   h.reserve(n_floats);
   for (int o = 0; o < 100; ++o)
@@ -2038,33 +2057,80 @@ bcts_status bcts_set_mlp(bcts_ctx* c, int32_t A, const float* blob, size_t n_flo
   for (int a = 0; a < A; ++a)
     for (int o = 0; o < 100; ++o) h.push_back(l1w[(size_t)o * (100 + A) + 100 + a]);
   h.insert(h.end(), rest, blob + n_floats);
+  // device copy: the matrices fragment-major, the vectors padded (see MlpDev)
+  std::vector<float> dv;
+  size_t at[14], src = 0;
+  int seg = 0;
+  auto frags = [&](const float* W, int units, int nf) {
+    at[seg++] = dv.size();
+    for (int f = 0; f < nf; ++f)
+      for (int j = 0; j < kMlpSteps4; ++j)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int t = 0; t < 4; ++t) {
+            const int i = lane & 15, u = 16 * f + 4 * (i & 3) + (i >> 2), k = 16 * j + 4 * t + (lane >> 4);
+            dv.push_back(u < units && k < 100 ? W[(size_t)u * 100 + k] : 0.f);
+          }
+  };
+  auto rows = [&](const float* v, int nrows, int len, int pad) {
+    at[seg++] = dv.size();
+    for (int i = 0; i < nrows; ++i)
+      for (int j = 0; j < pad; ++j) dv.push_back(j < len ? v[(size_t)i * len + j] : 0.f);
+    while (dv.size() % 4) dv.push_back(0.f);
+  };
+  auto next = [&](size_t k) { const float* p = h.data() + src; src += k; return p; };
+  const float *w1s = next(100 * 100), *w1a = next((size_t)A * 100), *b1 = next(100), *w2 = next(100 * 100),
+              *b2 = next(100), *w3 = next(100 * 100), *b3 = next(100), *wo = next(101 * 100), *bo = next(101),
+              *wq = next((size_t)A * 100), *bq = next(A);
+  frags(w1s, 100, kMlpFrags);
+  frags(w2, 100, kMlpFrags);
+  frags(w3, 100, kMlpFrags);
+  frags(wo, 101, kMlpFrags);
+  frags(wq, A, kMlpHeadFrags);
+  rows(w1a, A, 100, kMlpPad);
+  rows(b1, 1, 100, kMlpPad);
+  rows(b2, 1, 100, kMlpPad);
+  rows(b3, 1, 100, kMlpPad);
+  rows(bo, 1, 101, kMlpPad);
+  rows(bq, 1, A, 16 * kMlpHeadFrags);
+  rows(wq, A, 100, 100);
+  rows(bq, 1, A, A);
+  at[seg++] = dv.size();
+  {
+    // the large-level kernel's LDS image (see kMlpImage)
+    std::vector<float> img(kMlpImage, 0.f);
+    const float* Wl[4] = {w1s, w2, w3, wo};
+    for (int l = 0; l < 4; ++l)
+      for (int f = 0; f < kMlpFrags; ++f) {
+        const bool full = f + 1 < kMlpFrags;
+        const int per = full ? 16 : l < 3 ? 4 : 5, rows = 4 * per;
+        float* o = img.data() + l * 10000 + f * 1600;
+        for (int g = 0; g < 4; ++g)
+          for (int p = 0; p < per; ++p)
+            for (int st = 0; st < 25; ++st) {
+              // full fragments: slot = lane, row p of the fragment; else unit 96 + p
+              const int slot = g * per + p, u = full ? 16 * f + 4 * (p & 3) + (p >> 2) : 96 + p;
+              const float v = Wl[l][(size_t)u * 100 + 4 * st + g];
+              o[st < 24 ? ((st >> 2) * rows + slot) * 4 + (st & 3) : 24 * rows + slot] = v;
+            }
+      }
+    const float* bl[4] = {b1, b2, b3, bo};
+    for (int l = 0; l < 4; ++l) std::copy(bl[l], bl[l] + (l < 3 ? 100 : 101), img.begin() + kMlpImageBias + 100 * l);
+    dv.insert(dv.end(), img.begin(), img.end());
+  }
   if (c->mlp_mem) {
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     HIPCHECK(c, hipFree(c->mlp_mem));
     c->mlp_mem = nullptr;
     c->mlp_set = false;
   }
-  HIPCHECK(c, hipMalloc(&c->mlp_mem, sizeof(float) * h.size()));
-  HIPCHECK(c, hipMemcpy(c->mlp_mem, h.data(), sizeof(float) * h.size(), hipMemcpyHostToDevice));
+  HIPCHECK(c, hipMalloc(&c->mlp_mem, sizeof(float) * dv.size()));
+  HIPCHECK(c, hipMemcpy(c->mlp_mem, dv.data(), sizeof(float) * dv.size(), hipMemcpyHostToDevice));
   mlp_host_prepare(c->mlp_h, A, h.data());
-  auto carve = [&](const float* d0, auto& m) {
-    size_t o = 0;
-    auto next = [&](size_t k) { const float* p = d0 + o; o += k; return p; };
-    m.A = A;
-    m.w1s = next(100 * 100);
-    m.w1a = next((size_t)A * 100);
-    m.b1 = next(100);
-    m.w2 = next(100 * 100);
-    m.b2 = next(100);
-    m.w3 = next(100 * 100);
-    m.b3 = next(100);
-    m.wo = next(101 * 100);
-    m.bo = next(101);
-    m.wq = next((size_t)A * 100);
-    m.bq = next(A);
-  };
+  const float* d0 = static_cast<const float*>(c->mlp_mem);
   MlpDev m;
-  carve(static_cast<const float*>(c->mlp_mem), m);
+  m.A = A;
+  const float** dst[14] = {&m.f1, &m.f2, &m.f3, &m.fo, &m.fq, &m.w1a, &m.b1, &m.b2, &m.b3, &m.bo, &m.bqp, &m.wq, &m.bq, &m.image};
+  for (int i = 0; i < 14; ++i) *dst[i] = d0 + at[i];
   c->mlp = m;
   c->mlp_set = true;
   return BCTS_OK;

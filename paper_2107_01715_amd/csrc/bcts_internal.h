@@ -81,19 +81,48 @@ struct QnetDev {
   const void* wf8k[5];         // e4m3, conv2 / conv3 for the K = 128 instruction (launch_fragment_major_k128)
 };
 
-// Learned forward-model world: weights on the device, FP32, [out][in] rows of
-// 100 inputs.  l1's state part and its one-hot action columns are split so
-// that an action adds one column: w1a[a][o] = l1.w[o][100 + a].
+// Learned forward-model world: weights on the device, FP32.  The four layers
+// (l1's state part, l2, l3, out) and the head are stored fragment-major for
+// the matrix instruction: load j of unit fragment f gives lane (g = lane / 16,
+// i = lane % 16) the weights of unit 16 f + 4 (i % 4) + i / 4 for K = 16 j +
+// 4 t + g, t = 0..3 (zero past the layer's units and inputs).  l1's one-hot
+// action columns are rows w1a[a][o] = l1.w[o][100 + a], padded like the
+// biases; the root kernel reads the head as rows wq [A][100].
+constexpr int kMlpFrags = 7, kMlpSteps4 = 7, kMlpPad = 16 * kMlpFrags;
+constexpr int kMlpFragFloats = kMlpSteps4 * 64 * 4;      // one unit fragment
+constexpr int kMlpHeadFrags = (kMaxA + 15) / 16;
+// The four layers as the large-level kernel keeps them in LDS: layer l at
+// 10,000 l floats, its fragments without padding (fragment f < 6: [6][64
+// lanes][4] for K steps 4 j + t, then [64] for the 25th; the last: [6][R][4],
+// [R] with slot 4 g + p for unit 96 + p, R = 16, and in the output layer slot
+// 5 g + p, R = 20, p = 4 unit 100), then the biases, 100 a layer.
+constexpr int kMlpImageBias = 3 * 10000 + 10100, kMlpImage = kMlpImageBias + 412;
 struct MlpDev {
   int A;
-  const float *w1s, *w1a, *b1, *w2, *b2, *w3, *b3, *wo, *bo, *wq, *bq;
+  const float* image;
+  const float *f1, *f2, *f3, *fo, *fq;                   // fragment-major
+  const float *w1a, *b1, *b2, *b3, *bo, *bqp;            // rows of kMlpPad (bqp: 16 kMlpHeadFrags)
+  const float *wq, *bq;
 };
+// Levels of this many children and more run a wavefront per 64 children, with
+// the activations in registers; smaller ones split each 16 children over
+// seven wavefronts (see mlp.hip).
+constexpr long long kMlpLarge = 32768;
 void launch_mlp_level(const MlpDev& m, long long n, const float* ps, const float* pret, float gpow, float* os,
                       float* oret, float* ov, float* oleaf, float gamma_d, hipStream_t s);
+// `levels` levels in one launch, each workgroup the sub-tree of one node
+// (levels > 1 needs A^levels <= 16): n children at the first level; ps, pret
+// its parents; gpow[levels]; os / oret the last level's states and returns,
+// ret1 / ov the first level's returns and head values, oleaf the last's leaf
+// values (null: not kept).
+void launch_mlp_levels(const MlpDev& m, long long n, int levels, const float* ps, const float* pret,
+                       const float* gpow, float* os, float* oret, float* ret1, float* ov, float* oleaf, float gamma_d,
+                       hipStream_t s);
 void launch_mlp_blockmax(long long n_blocks, long long block, const float* leaf, float* qd, hipStream_t s);
+// leaf non-null: the root kernel takes the block maxima itself (qd unused)
 void launch_mlp_root(const MlpDev& m, int n, int d, const float* states, const float* ret1, const float* v1,
-                     const float* qd, float gamma, float gamma_d, float pen_e, float pen_o, int corr, float scale,
-                     int32_t* act, float* q, hipStream_t s);
+                     const float* leaf, long long block, const float* qd, float gamma, float gamma_d, float pen_e,
+                     float pen_o, int corr, float scale, int32_t* act, float* q, hipStream_t s);
 
 // Copies W[N][K] (element size eb bytes) into fragment-major order; with
 // pair8 (conv2, conv3: N = 64) the rows of channel fragments 2h, 2h + 1 are

@@ -189,3 +189,22 @@ def test_crossover_argument(lib, model):
         ctx.set_tuning(lib.TUNE_MLP_CROSSOVER, 17)
     assert e.value.status == lib.E_INVAL
     assert ctx.get_tuning(lib.TUNE_MLP_CROSSOVER) == 0
+
+
+@pytest.mark.parametrize("A,n,d", [
+    (2, 1, 1), (2, 3, 4), (2, 1, 10),      # sub-trees of 4 levels per launch, with and without a remainder
+    (3, 5, 5), (4, 7, 3),                  # of 2 levels (9 and 16 leaves)
+    (18, 1, 2), (18, 3, 2),                # one level per launch, two fragments of head actions
+    (18, 102, 2),                          # 33,048 children: the large-level kernel, a ragged last tile
+    (2, 1, 14),                            # 16,384 leaves per root: block maxima in their own kernel
+])
+def test_level_kernels_equal_host_search(lib, A, n, d):
+    """Every level kernel sums in the host search's order: the same bits."""
+    ctx = lib.Context(0)
+    ctx.set_mlp(A, W.mlp_blob(W.mlp_weights(11, A), A))
+    st, corr = W.mlp_states(105 + n, n), lib.correction(True, 1.0)
+    a0, q0 = ctx.mlp_search(st, d, A, GAMMA, corr)
+    ctx.set_tuning(lib.TUNE_MLP_HOST, 1)
+    a1, q1 = ctx.mlp_search(st, d, A, GAMMA, corr)
+    assert np.array_equal(a0, a1) and np.array_equal(q0, q1), np.abs(q0 - q1).max()
+    ctx.close()

@@ -316,12 +316,21 @@ bcts_status launch_gate(bcts_ctx* c) {
   return BCTS_OK;
 }
 
-FrameBases frame_bases(const Plan& p, char* A, const uint8_t* d_stacks) {
+// Whether the Q-network reads a leaf as its positions (the sibling kernel
+// forms the frame) rather than as a rendered frame.  Level 1 is rendered all
+// the same: the correction's FP32 evaluations read its frames.
+// With BCTS_TUNE_FP8_K128 off FP8 keeps to the group kernel's K = 32 path.
+bool leaf_positions(const bcts_ctx* c, const Plan& p) {
+  return p.fused && (c->prec == P_BF16 || (c->prec == P_FP8 && c->fp8_k128));
+}
+
+FrameBases frame_bases(const bcts_ctx* c, const Plan& p, char* A, const uint8_t* d_stacks) {
   FrameBases fb{};
   fb.level_frames[0] = d_stacks;
   for (int k = 1; k <= p.maxd; ++k) {
     fb.level_frames[k] = reinterpret_cast<const uint8_t*>(A + p.o_frames[k]);
     fb.keep[k] = p.keep_count[k] > 0 ? reinterpret_cast<const int*>(A + p.o_keep[k]) : nullptr;
+    fb.leaf_pos[k] = leaf_positions(c, p) ? reinterpret_cast<const uint8_t*>(A + p.o_pos[k]) : nullptr;
   }
   return fb;
 }
@@ -335,11 +344,13 @@ bcts_status enqueue_level(bcts_ctx* c, const Plan& p, char* A, int k, const int3
   const float g = discount_f32(gamma, k - 1);    // the FP32 discount a pruned search ranks by
   LevelRoots lr{reinterpret_cast<const int*>(A + p.o_lroot[k]), reinterpret_cast<const long long*>(A + p.o_lstart[k]),
                 (int)p.lvl_root[k].size()};
+  bool inner = false;
+  for (int r : p.lvl_root[k]) inner = inner || p.roots[r].d > k;
   launch_expand(k, p.lvl_count[k], lr, roots, d_pos,
                 k > 1 ? reinterpret_cast<const uint8_t*>(A + p.o_pos[k - 1]) : nullptr,
                 k > 1 ? reinterpret_cast<const float*>(A + p.o_ret[k - 1]) : nullptr,
                 k > 1 && p.keep_count[k - 1] > 0 ? reinterpret_cast<const int*>(A + p.o_keep[k - 1]) : nullptr,
-                c->env, g, reinterpret_cast<uint8_t*>(A + p.o_pos[k]), reinterpret_cast<uint8_t*>(A + p.o_frames[k]),
+                c->env, g, !leaf_positions(c, p) || k < 2, inner, reinterpret_cast<uint8_t*>(A + p.o_pos[k]), reinterpret_cast<uint8_t*>(A + p.o_frames[k]),
                 reinterpret_cast<float*>(A + p.o_ret[k]), reinterpret_cast<uint8_t*>(A + p.o_rew[k]), s);
   if (p.keep_count[k] > 0)
     launch_prune(k, (int)p.lvl_root[k].size(), lr, roots, reinterpret_cast<const float*>(A + p.o_ret[k]),
@@ -400,7 +411,10 @@ bcts_status enqueue_qnet_chunk(bcts_ctx* c, const Plan& p, char* A, ItemDesc* de
   char* h = x3 + fused_x3_bytes(p.chunk, c->prec);
   fa.x3 = x3;
   if (cev) HIPCHECK(c, hipEventRecord(cev[0], s));
-  launch_conv_fused(c->prec, c->fused_T, fa, ch.g1 - ch.g0, s, c->fp8_k128);
+  const int n_groups = ch.g1 - ch.g0;
+  fa.skip_leaves = leaf_positions(c, p) ? 1 : 0;
+  if (fa.skip_leaves && ch.leaf_groups > 0) launch_conv_siblings(c->prec, fa, n_groups, s);
+  if (!fa.skip_leaves || ch.leaf_groups < n_groups) launch_conv_fused(c->prec, c->fused_T, fa, n_groups, s, c->fp8_k128);
   if (cev) {
     HIPCHECK(c, hipEventRecord(cev[1], s));
     HIPCHECK(c, hipEventRecord(cev[2], s));
@@ -489,7 +503,7 @@ bcts_status enqueue_search_at(bcts_ctx* c, const Plan& p, char* A, const int32_t
     if ((st = enqueue_level(c, p, A, k, d_pos, gamma, s)) != BCTS_OK) return st;
     if (timed) HIPCHECK(c, hipEventRecord(ev[k], s));
   }
-  const FrameBases fb = frame_bases(p, A, d_stacks);
+  const FrameBases fb = frame_bases(c, p, A, d_stacks);
   if ((st = enqueue_qnet_stage(c, p, A, fb, s, timed ? ev + 1 + p.maxd : nullptr)) != BCTS_OK) return st;
   if (timed) HIPCHECK(c, hipEventRecord(ev[3 + p.maxd + 6 * nchunks], s));
   if ((st = enqueue_backup(c, p, A, gamma, corr_scale, d_act, d_q, s)) != BCTS_OK) return st;
@@ -865,7 +879,7 @@ struct ServeEngine {
     }
     const int nl = p.maxd, nc = (int)p.chunks.size(), nt = p.tail_chunks.empty() ? 0 : 1;
     if (i < nl) return enqueue_level(c, p, A, i + 1, d_pos, k.gamma, stream);
-    const FrameBases fb = frame_bases(p, A, d_stacks);
+    const FrameBases fb = frame_bases(c, p, A, d_stacks);
     if (i < nl + nc) return enqueue_qnet_chunk(c, p, A, desc, ws, fb, i - nl, stream, nullptr);
     if (i < nl + nc + nt) return enqueue_tail(c, p, A, desc, ws, fb, stream);
     int32_t* d_act = reinterpret_cast<int32_t*>(A + p.o_act);
@@ -1499,7 +1513,7 @@ bcts_status bcts_debug_expand(bcts_ctx* c, const int32_t* pos, const uint8_t* st
     launch_expand(k, p.lvl_count[k], lr, roots, reinterpret_cast<const int32_t*>(Ar + p.o_root_pos),
                   k > 1 ? reinterpret_cast<const uint8_t*>(Ar + p.o_pos[k - 1]) : nullptr,
                   k > 1 ? reinterpret_cast<const float*>(Ar + p.o_ret[k - 1]) : nullptr, nullptr, c->env, 1.f,
-                  reinterpret_cast<uint8_t*>(Ar + p.o_pos[k]), reinterpret_cast<uint8_t*>(Ar + p.o_frames[k]),
+                  true, true, reinterpret_cast<uint8_t*>(Ar + p.o_pos[k]), reinterpret_cast<uint8_t*>(Ar + p.o_frames[k]),
                   reinterpret_cast<float*>(Ar + p.o_ret[k]), reinterpret_cast<uint8_t*>(Ar + p.o_rew[k]), s);
   }
   HIPCHECK(c, hipGetLastError());

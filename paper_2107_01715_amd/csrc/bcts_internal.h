@@ -37,6 +37,10 @@ struct LevelRoots {
 struct FrameBases {
   const uint8_t* level_frames[kMaxD + 1];
   const int* keep[kMaxD + 1];  // keep lists of cut levels (root-local node indices)
+  // positions [N_k][16] of the levels whose leaves the Q-network reads as
+  // positions: a leaf's descriptor then holds its position row instead of
+  // its own frame (null: frames)
+  const uint8_t* leaf_pos[kMaxD + 1];
 };
 
 // Parent of root-local node j at level k >= 2: node j / A of level k - 1
@@ -51,6 +55,7 @@ __device__ __forceinline__ long long parent_local(const RootInfo& ri, const int*
 struct FusedConvArgs {
   const FusedGroup* groups;    // groups of this chunk
   int n_groups;                // groups in the chunk (the kernel loops over them)
+  int skip_leaves;             // the group kernel leaves groups of leaves to the sibling kernel
   long long item_base;         // plan-global index of desc[0]
   const ItemDesc* desc;        // chunk-relative item descriptors
   const void* w[3];            // conv weights in operand type: conv1 [N][K], conv2/conv3 fragment-major
@@ -62,6 +67,12 @@ struct FusedConvArgs {
 };
 // k8: FP8 conv2 / conv3 on the K = 128 instruction (weights in wf8k).
 void launch_conv_fused(int prec, int T, const FusedConvArgs& a, int n_groups, hipStream_t s, bool k8 = false);
+
+// The same layers for the groups of leaves among the chunk's: their
+// descriptors' frame[3] is the leaf's position row, from which the kernel
+// forms the leaf's own frame.  FP8 takes the K = 128 weight copies (wf8k).
+// Results equal launch_conv_fused's on rendered frames bit for bit.
+void launch_conv_siblings(int prec, const FusedConvArgs& a, int n_groups, hipStream_t s);
 
 // Device weights in GEMM layout W[N][K] for every precision.  K orders:
 // conv1 (c, kh, kw); conv2, conv3 (kh, kw, c); fc1 (h, w, c); fc2 (k).
@@ -168,10 +179,12 @@ void launch_qnet_fc(int prec, const QnetDev& q, const ItemDesc* desc, long long 
                     hipEvent_t ev_after_fc1, bool fc2_folded);
 
 // ---- launchers (each in the TU that defines its kernels) ----------------
+// `leaf_frames` false: the leaves (nodes of roots of depth k) get no frame;
+// `any_inner` false: the level holds leaves only.
 void launch_expand(int k, long long n_nodes, LevelRoots lr, const RootInfo* roots,
                    const int* root_pos, const uint8_t* prev_pos, const float* prev_ret, const int* prev_keep,
-                   const EnvTables& env, float gamma_pow, uint8_t* pos, uint8_t* frames,
-                   float* ret, uint8_t* rew, hipStream_t s);
+                   const EnvTables& env, float gamma_pow, bool leaf_frames, bool any_inner, uint8_t* pos,
+                   uint8_t* frames, float* ret, uint8_t* rew, hipStream_t s);
 
 // Beam cut of level k: for every root whose level k is cut and every root
 // action a0, the `beam` nodes of a0's block with the largest return (lowest

@@ -14,6 +14,10 @@
 //   3. per (node, 16-byte chunk of the flat frame): expand the masks to
 //      bytes and store 16 B -- consecutive threads write consecutive chunks,
 //      so every wavefront store covers 1 KiB of contiguous HBM.
+// Steps 2 and 3 pass over leaves the Q-network reads as positions (the
+// sibling kernel forms their frames); a level of nothing else runs in
+// move_kernel, one thread per node: 27 us for 1.49 M leaves, against 1.9 ms
+// with their frames written.
 #include "bcts_internal.h"
 
 namespace bcts {
@@ -125,16 +129,87 @@ prune_kernel(int k, LevelRoots lr, const RootInfo* __restrict__ roots, const flo
   }
 }
 
+// Everything of a node but its frame: its positions (left in p as well),
+// return and reward.  Returns the node's root.
+struct LevelStep {
+  int k;
+  LevelRoots lr;
+  const RootInfo* roots;
+  const int* root_pos;
+  const uint8_t* prev_pos;
+  const float* prev_ret;
+  const int* prev_keep;
+  EnvTables env;
+  float gamma_pow;
+  uint8_t* pos;
+  float* ret;
+  uint8_t* rew;
+};
+__device__ __forceinline__ int step_node(const LevelStep& v, long long node, int (&p)[kSprites][2]) {
+  const int k = v.k;
+  const RootInfo* roots = v.roots;
+  const int ri = find_root(v.lr, node);
+  const int r = v.lr.root[ri];
+  const long long j = node - v.lr.start[ri];
+  const int A = roots[r].A;
+  const int a = (int)(j % A);
+  const long long pj = roots[r].kbase[k - 1] >= 0 && k > 1 ? (long long)v.prev_keep[roots[r].kbase[k - 1] + j / A]
+                                                          : j / A;
+  float pret = 0.f;
+  if (k == 1) {
+    const int* rp = v.root_pos + (long long)r * kSprites * 2;
+    for (int i = 0; i < kSprites; ++i) {
+      p[i][0] = wrap84(rp[2 * i]);
+      p[i][1] = wrap84(rp[2 * i + 1]);
+    }
+  } else {
+    const long long pn = roots[r].base[k - 1] + pj;
+    const uint4 u = *reinterpret_cast<const uint4*>(v.prev_pos + pn * 16);
+    const unsigned w[4] = {u.x, u.y, u.z, u.w};
+    for (int i = 0; i < kSprites; ++i) {
+      const unsigned word = w[i >> 1] >> ((i & 1) * 16);
+      p[i][0] = word & 255u;
+      p[i][1] = (word >> 8) & 255u;
+    }
+    pret = v.prev_ret[pn];
+  }
+  p[0][0] = wrap84(p[0][0] + v.env.delta[a][0]);
+  p[0][1] = wrap84(p[0][1] + v.env.delta[a][1]);
+  for (int i = 1; i < kSprites; ++i) {
+    p[i][0] = wrap84(p[i][0] + v.env.vel[i - 1][0]);
+    p[i][1] = wrap84(p[i][1] + v.env.vel[i - 1][1]);
+  }
+  int rew = 0;
+  for (int i = 1; i < kSprites; ++i) {
+    int dx = wrap84(p[0][0] - p[i][0]), dy = wrap84(p[0][1] - p[i][1]);
+    dx = dx < kFrame - dx ? dx : kFrame - dx;
+    dy = dy < kFrame - dy ? dy : kFrame - dy;
+    rew += (dx < 6 && dy < 6) ? 1 : 0;
+  }
+  unsigned w[4];
+  for (int q = 0; q < 4; ++q)
+    w[q] = (unsigned)p[2 * q][0] | ((unsigned)p[2 * q][1] << 8) |
+           ((unsigned)p[2 * q + 1][0] << 16) | ((unsigned)p[2 * q + 1][1] << 24);
+  *reinterpret_cast<uint4*>(v.pos + node * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+  v.ret[node] = fmaf(v.gamma_pow, (float)rew, pret);   // one rounding (a beam ranks these)
+  v.rew[node] = (uint8_t)rew;
+  return r;
+}
+
+// A level without frames, one thread per node.
+__global__ void __launch_bounds__(kThreads) move_kernel(LevelStep v, long long n_nodes) {
+  const long long node = (long long)blockIdx.x * kThreads + threadIdx.x;
+  int p[kSprites][2];
+  if (node < n_nodes) step_node(v, node, p);
+}
+
 __global__ void __launch_bounds__(kThreads)
-expand_kernel(int k, long long n_nodes, LevelRoots lr, const RootInfo* __restrict__ roots,
-              const int* __restrict__ root_pos, const uint8_t* __restrict__ prev_pos,
-              const float* __restrict__ prev_ret, const int* __restrict__ prev_keep, EnvTables env, float gamma_pow,
-              uint8_t* __restrict__ pos, uint8_t* __restrict__ frames, float* __restrict__ ret,
-              uint8_t* __restrict__ rew_out) {
+expand_kernel(LevelStep v, long long n_nodes, int leaf_frames, uint8_t* __restrict__ frames) {
   __shared__ int s_pos[kNB][kSprites][2];
   __shared__ RowMask s_rows[kNB][kFrame];
   __shared__ unsigned long long s_clo[kNB][kSprites];
   __shared__ unsigned s_chi[kNB][kSprites];
+  __shared__ int s_draw[kNB];
 
   const int tid = threadIdx.x;
   for (long long g0 = (long long)blockIdx.x * kNB; g0 < n_nodes; g0 += (long long)gridDim.x * kNB) {
@@ -142,53 +217,9 @@ expand_kernel(int k, long long n_nodes, LevelRoots lr, const RootInfo* __restric
 
     // 1. move and score, one thread per node
     if (tid < nb) {
-      const long long node = g0 + tid;
-      const int ri = find_root(lr, node);
-      const int r = lr.root[ri];
-      const long long j = node - lr.start[ri];
-      const int A = roots[r].A;
-      const int a = (int)(j % A);
-      const long long pj = roots[r].kbase[k - 1] >= 0 && k > 1 ? (long long)prev_keep[roots[r].kbase[k - 1] + j / A]
-                                                              : j / A;
       int p[kSprites][2];
-      float pret = 0.f;
-      if (k == 1) {
-        const int* rp = root_pos + (long long)r * kSprites * 2;
-        for (int i = 0; i < kSprites; ++i) {
-          p[i][0] = wrap84(rp[2 * i]);
-          p[i][1] = wrap84(rp[2 * i + 1]);
-        }
-      } else {
-        const long long pn = roots[r].base[k - 1] + pj;
-        const uint4 v = *reinterpret_cast<const uint4*>(prev_pos + pn * 16);
-        const unsigned w[4] = {v.x, v.y, v.z, v.w};
-        for (int i = 0; i < kSprites; ++i) {
-          const unsigned word = w[i >> 1] >> ((i & 1) * 16);
-          p[i][0] = word & 255u;
-          p[i][1] = (word >> 8) & 255u;
-        }
-        pret = prev_ret[pn];
-      }
-      p[0][0] = wrap84(p[0][0] + env.delta[a][0]);
-      p[0][1] = wrap84(p[0][1] + env.delta[a][1]);
-      for (int i = 1; i < kSprites; ++i) {
-        p[i][0] = wrap84(p[i][0] + env.vel[i - 1][0]);
-        p[i][1] = wrap84(p[i][1] + env.vel[i - 1][1]);
-      }
-      int rew = 0;
-      for (int i = 1; i < kSprites; ++i) {
-        int dx = wrap84(p[0][0] - p[i][0]), dy = wrap84(p[0][1] - p[i][1]);
-        dx = dx < kFrame - dx ? dx : kFrame - dx;
-        dy = dy < kFrame - dy ? dy : kFrame - dy;
-        rew += (dx < 6 && dy < 6) ? 1 : 0;
-      }
-      unsigned w[4];
-      for (int q = 0; q < 4; ++q)
-        w[q] = (unsigned)p[2 * q][0] | ((unsigned)p[2 * q][1] << 8) |
-               ((unsigned)p[2 * q + 1][0] << 16) | ((unsigned)p[2 * q + 1][1] << 24);
-      *reinterpret_cast<uint4*>(pos + node * 16) = make_uint4(w[0], w[1], w[2], w[3]);
-      ret[node] = fmaf(gamma_pow, (float)rew, pret);   // one rounding (a beam ranks these)
-      rew_out[node] = (uint8_t)rew;
+      const int r = step_node(v, g0 + tid, p);
+      s_draw[tid] = leaf_frames || v.roots[r].d != v.k;
       for (int i = 0; i < kSprites; ++i) {
         s_pos[tid][i][0] = p[i][0];
         s_pos[tid][i][1] = p[i][1];
@@ -218,6 +249,7 @@ expand_kernel(int k, long long n_nodes, LevelRoots lr, const RootInfo* __restric
     // 3. 16-byte chunks of the frames
     for (int t = tid; t < nb * kChunks; t += kThreads) {
       const int b = t / kChunks, c = t % kChunks;
+      if (!s_draw[b]) continue;
       const int o = c * 16, y0 = o / kFrame, x0 = o % kFrame;
       const int len0 = (kFrame - x0) < 16 ? (kFrame - x0) : 16;
       const RowMask& r0 = s_rows[b][y0];
@@ -243,9 +275,15 @@ expand_kernel(int k, long long n_nodes, LevelRoots lr, const RootInfo* __restric
 
 void launch_expand(int k, long long n_nodes, LevelRoots lr, const RootInfo* roots,
                    const int* root_pos, const uint8_t* prev_pos, const float* prev_ret, const int* prev_keep,
-                   const EnvTables& env, float gamma_pow, uint8_t* pos, uint8_t* frames,
-                   float* ret, uint8_t* rew, hipStream_t s) {
+                   const EnvTables& env, float gamma_pow, bool leaf_frames, bool any_inner, uint8_t* pos,
+                   uint8_t* frames, float* ret, uint8_t* rew, hipStream_t s) {
   if (n_nodes <= 0) return;
+  const LevelStep v{k, lr, roots, root_pos, prev_pos, prev_ret, prev_keep, env, gamma_pow, pos, ret, rew};
+  if (!leaf_frames && !any_inner) {
+    hipLaunchKernelGGL(move_kernel, dim3((unsigned)((n_nodes + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, v,
+                       n_nodes);
+    return;
+  }
   // One workgroup per group of kNB nodes (the loop covers grids capped at
   // 2^20 workgroups).  Measured on the 1.49M-node level of the headline
   // shape: capping the grid at 65,536 workgroups that loop over several
@@ -253,8 +291,7 @@ void launch_expand(int k, long long n_nodes, LevelRoots lr, const RootInfo* root
   // level's HBM write stream (the three levels take 8% longer with both).
   long long groups = (n_nodes + kNB - 1) / kNB;
   int grid = (int)(groups < (1 << 20) ? groups : (1 << 20));
-  hipLaunchKernelGGL(expand_kernel, dim3(grid), dim3(kThreads), 0, s, k, n_nodes, lr, roots,
-                     root_pos, prev_pos, prev_ret, prev_keep, env, gamma_pow, pos, frames, ret, rew);
+  hipLaunchKernelGGL(expand_kernel, dim3(grid), dim3(kThreads), 0, s, v, n_nodes, leaf_frames ? 1 : 0, frames);
 }
 
 void launch_prune(int k, int n_level_roots, LevelRoots lr, const RootInfo* roots, const float* ret_k, int* keep_k,

@@ -81,7 +81,7 @@ struct ItemDesc {
 struct FusedGroup {
   long long item0;             // first item (plan-global index)
   int count;
-  int pad_;
+  int leaf;                    // 1: the leaves below one node of the tree
 };
 
 }  // namespace bcts

@@ -88,11 +88,13 @@ void make_chunks(const Plan& p, int g, int g_end, long long target, std::vector<
     ch.i0 = p.groups[g].item0;
     ch.max_group = 0;
     ch.group_stages = 0;
+    ch.leaf_groups = 0;
     long long items = 0;
     while (g < g_end && (items == 0 || items + p.groups[g].count <= target)) {
       items += p.groups[g].count;
       ch.max_group = std::max(ch.max_group, p.groups[g].count);
       ch.group_stages += 6 + 2LL * p.groups[g].count;
+      ch.leaf_groups += p.groups[g].leaf;
       ++g;
     }
     ch.g1 = g;
@@ -206,7 +208,7 @@ void make_plan(Plan& p, int n, const int32_t* depth, const int32_t* A, float gam
     const RootInfo& ri = p.roots[sg.root];
     const long long cnt = sg.kind == 2 ? 1 : (sg.kind == 1 ? ri.A : ri.lcnt[ri.d]);
     const int gsz = sg.kind == 2 ? 1 : ri.A;
-    for (long long j = 0; j < cnt; j += gsz) p.groups.push_back(FusedGroup{sg.item0 + j, gsz, 0});
+    for (long long j = 0; j < cnt; j += gsz) p.groups.push_back(FusedGroup{sg.item0 + j, gsz, sg.kind == 0 ? 1 : 0});
   }
   if (main_segs == p.segs.size()) main_groups = (int)p.groups.size();
   p.chunk = 1;

@@ -53,10 +53,10 @@ struct Plan {
   long long chunk = 0;                 // max items of a chunk
   bool fused = false;                  // conv stack fused per sibling group
   std::vector<FusedGroup> groups;      // sibling groups in item order (main items, then the tail's)
-  // A chunk: groups [g0, g1), items [i0, i1); its largest group and the sum
+  // A chunk: groups [g0, g1), items [i0, i1); its largest group, the sum
   // over its groups of (6 + 2 x group size), the conv1 stages of the group
-  // kernel per 128 pixel rows
-  struct Chunk { int g0, g1; long long i0, i1; int max_group; long long group_stages; };
+  // kernel per 128 pixel rows, and its groups of leaves
+  struct Chunk { int g0, g1; long long i0, i1; int max_group; long long group_stages; int leaf_groups; };
   std::vector<Chunk> chunks;           // whole groups of the main items, ~chunk_items items each
   // The correction's own Q-network inputs (the root and depth-1 evaluations
   // of corrected roots) can run in FP32 whatever the leaf precision: they

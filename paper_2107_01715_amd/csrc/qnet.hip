@@ -762,6 +762,7 @@ __global__ void item_desc_kernel(long long item_begin, long long n_items, const 
       d.frame[c] = fb.level_frames[0] + ((long long)sg.root * 4 + 3 + l) * (long long)kFrameBytes;
     }
   }
+  if (sg.kind == 0 && fb.leaf_pos[m]) d.frame[3] = fb.leaf_pos[m] + (ri.base[m] + j) * 16;
   d.A = sg.A;
   d.q0_root = sg.kind == 2 ? sg.root : -1;
   out[t] = d;

@@ -366,6 +366,205 @@ fc1_kernel(long long n, const unsigned char* __restrict__ X, const unsigned char
   }
 }
 
+__device__ __forceinline__ void load_lds16(const unsigned char* src, unsigned char* dst) {
+  __builtin_amdgcn_global_load_lds(src, (void __attribute__((address_space(3)))*)dst, 16, 0, 0);
+}
+
+// fc1 for fewer stacks, where 256 x 256 tiles leave most of the chip idle: H
+// from BM x BN tiles of (NWM x NWN) wavefronts, each wavefront's sums those of
+// fc1_kernel (the same matrix instructions over K in the same order, so the
+// same bits).  Stages as there, taken two at a time: one barrier per pair, a
+// ring of three pairs, pair p + 2 requested once every wavefront has passed
+// pair p's barrier and so has finished pair p - 1, whose slots it takes.
+// Bound by a block's serial walk over K (49 pairs in BF16): a ring of 4, 5 or
+// 8 pairs takes the same time, a smaller tile with its fewer fragments less.
+//
+// Which tile (us, BF16 / FP8; 32 x 32, 64 x 64, 128 x 128, 256 x 256):
+//      5 stacks   14/9    18/11   29/17   76/41
+//   1024          17/10   19/12   30/18   79/42
+//   1500          20/13   19/12   30/18   78/42
+//   4096          38/22   24/15   32/19   79/42
+//   6000          70/33   48/25   34/20   80/43
+//   8192          89/43   52/29   36/21   81/44
+//  16384         218/106 118/59   67/38   84/46
+//  24576                 179/90  103/55   90/49
+// A full round of 256 x 256 tiles (one block on each of 256 CUs) is 32,768
+// stacks, 98/52 us, so what n holds beyond whole rounds is a launch of its
+// own: 40,000 stacks 175/91 as one launch.
+constexpr int kPairs = 3;
+constexpr long long kFc1Tiny = 1024, kFc1Small = 4096, kFc1Medium = 16384, kFc1Round = 32768;
+template <int P, int BM, int BN, int NWM, int NWN>
+__global__ void __launch_bounds__(64 * NWM * NWN)
+fc1_tile_kernel(long long n, const unsigned char* __restrict__ X, const unsigned char* __restrict__ W,
+                const float* __restrict__ bias, float acc_scale, float out_s8, unsigned char* __restrict__ H) {
+  typedef FT<P> Ft;
+  typedef typename Ft::V V;
+  constexpr int EB = Ft::EB, KPS = kRB / EB, NST = kK / KPS, KS = KPS / 32;
+  constexpr int T = 64 * NWM * NWN, SB = (BM + BN) * kRB, PER = SB / (T * 16);   // loads per thread and stage
+  constexpr int FM = BM / NWM / 16, FN = BN / NWN / 16;                          // a wavefront's stack and neuron fragments
+  static_assert( kFc1Rows % BM == 0 && kFc1Rows % BN == 0 && SB % (T * 16) == 0, "tile shape");
+  static_assert(FN % 2 == 0 && 2 * PER * (kPairs - 2) < 64, "paired weight rows, loads in flight");
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[2 * kPairs][SB];
+  const long long m0 = (long long)blockIdx.x * BM;
+  const int n0 = blockIdx.y * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, g = lane >> 4;
+  const int wm = wave / NWN, wn = wave % NWN;
+
+  // 16-byte LDS slot ps = tid + j T of a stage: row ps / 4 of the X rows, then
+  // the W rows, physical chunk ps % 4; a stage of a tile is contiguous
+  const unsigned char* src[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int ps = tid + j * T, row = ps >> 2, r = row < BM ? row : row - BM;
+    const int c = (ps & 3) ^ swz_x<EB>(r);
+    src[j] = row < BM ? X + fc1_tiled_offset(m0 + r, c * 16, EB) : W + fc1_tiled_offset(n0 + r, c * 16, EB);
+  }
+  auto issue_pair = [&](int p) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int st = 2 * p + h;
+      if (st >= NST) continue;
+      unsigned char* base = ring[st % (2 * kPairs)] + wave * 1024;
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        load_lds16(src[j] + (long long)st * kFc1StageBytes, base + j * T * 16);
+    }
+  };
+  f32x4 acc[FN][FM];
+#pragma unroll
+  for (int i = 0; i < FN; ++i)
+#pragma unroll
+    for (int j = 0; j < FM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  constexpr int NP = (NST + 1) / 2;
+#pragma unroll
+  for (int p = 0; p < kPairs - 1; ++p) issue_pair(p);
+  for (int p = 0; p < NP; ++p) {
+    // this pair's loads done; the next pair's may be in flight
+    if (2 * (p + kPairs - 2) + 1 < NST) __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER * (kPairs - 2)) : "memory");
+    else __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+    if (2 * (p + kPairs - 1) < NST) issue_pair(p + kPairs - 1);
+    if (P == P_FP8 && 2 * p + 1 < NST) {
+      // one K = 128 step: this lane's K chunk is stage 2p + (g >> 1), bytes 32 (g & 1) ..
+      typedef __attribute__((ext_vector_type(8))) int v8i;
+      typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+      const unsigned char* As = ring[(2 * p + (g >> 1)) % (2 * kPairs)];
+      const unsigned char* Bs = As + BM * kRB;
+      const int c0 = 2 * (g & 1);
+      auto ld32 = [&](const unsigned char* b, int row) {
+        const u32x4 lo = *reinterpret_cast<const u32x4*>(b + swz<EB>(row, c0));
+        const u32x4 hi = *reinterpret_cast<const u32x4*>(b + swz<EB>(row, c0 + 1));
+        return v8i{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+      };
+      v8i xv[FM];
+#pragma unroll
+      for (int j = 0; j < FM; ++j) xv[j] = ld32(As, (wm * FM + j) * 16 + r16);
+#pragma unroll
+      for (int i = 0; i < FN; ++i) {
+        const v8i wv = ld32(Bs, (wn * FN + i) * 16 + r16);
+#pragma unroll
+        for (int j = 0; j < FM; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wv, xv[j], acc[i][j], 0, 0, 0, 127, 0, 127);
+      }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (2 * p + h >= NST) continue;
+        const unsigned char* As = ring[(2 * p + h) % (2 * kPairs)];
+        const unsigned char* Bs = As + BM * kRB;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const int kb = (ks * 32 + 8 * g) * EB, c = kb >> 4, cb = kb & 15;
+          V xv[FM];
+#pragma unroll
+          for (int j = 0; j < FM; ++j)
+            xv[j] = *reinterpret_cast<const V*>(As + swz<EB>((wm * FM + j) * 16 + r16, c) + cb);
+#pragma unroll
+          for (int i = 0; i < FN; ++i) {
+            const V wv = *reinterpret_cast<const V*>(Bs + swz<EB>((wn * FN + i) * 16 + r16, c) + cb);
+#pragma unroll
+            for (int j = 0; j < FM; ++j) acc[i][j] = Ft::mma(wv, xv[j], acc[i][j]);
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < FN / 2; ++k) {
+    const int nb = n0 + wn * FN * 16 + 32 * k + 8 * g;
+    float b[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) b[e] = bias[nb + e];
+#pragma unroll
+    for (int j = 0; j < FM; ++j) {
+      const long long m = m0 + (wm * FM + j) * 16 + r16;
+      if (m < n) {
+        float v[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[4 * h + q] = fmaxf(acc[2 * k + h][j][q] * acc_scale + b[4 * h + q], 0.f);
+        Ft::st8(H + (m * 512 + nb) * EB, v, out_s8);
+      }
+    }
+  }
+}
+
+// fc2 + max on H with the sum over the 512 neurons associated as
+// fc1_kernel<P, true> and fc2_sum_kernel do: four chains of 128, (0 + 1) +
+// (2 + 3).  A block per 16 stacks, a wavefront per chain.
+template <int P>
+__global__ void __launch_bounds__(256) fc2_quarters_kernel(long long n, const unsigned char* __restrict__ H,
+                                                           const unsigned char* __restrict__ W2,
+                                                           const float* __restrict__ bias, float scale,
+                                                           const ItemDesc* __restrict__ desc, float* __restrict__ V,
+                                                           float* __restrict__ q0) {
+  typedef FT<P> Ft;
+  typedef typename Ft::V Op;
+  constexpr int EB = Ft::EB;
+  __shared__ f32x4 part[4][2][64];
+  const int lane = threadIdx.x & 63, c = threadIdx.x >> 6, r16 = lane & 15, g = lane >> 4;
+  const long long m = (long long)blockIdx.x * 16 + r16;
+  const long long mm = m < n ? m : n - 1;
+  const int A = desc[mm].A, root = desc[mm].q0_root;
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int nb = 128 * c + 32 * k + 8 * g;
+    const Op h = *reinterpret_cast<const Op*>(H + (mm * 512 + nb) * EB);
+#pragma unroll
+    for (int af = 0; af < 2; ++af)
+      acc[af] = Ft::mma(*reinterpret_cast<const Op*>(W2 + ((size_t)(af * 16 + r16) * 512 + nb) * EB), h, acc[af]);
+  }
+  part[c][0][lane] = acc[0];
+  part[c][1][lane] = acc[1];
+  __syncthreads();
+  if (c) return;
+  float best = -INFINITY;
+  f32x4 qv[2];
+#pragma unroll
+  for (int af = 0; af < 2; ++af)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int a = 16 * af + 4 * g + q;
+      const float lo = acc[af][q] + part[1][af][lane][q], hi = part[2][af][lane][q] + part[3][af][lane][q];
+      qv[af][q] = fmaf(lo + hi, scale, a < kMaxA ? bias[a] : 0.f);
+      if (a < A) best = fmaxf(best, qv[af][q]);
+    }
+  best = fmaxf(best, __shfl_xor(best, 16));
+  best = fmaxf(best, __shfl_xor(best, 32));
+  if (m >= n) return;
+  if (g == 0) V[m] = best;
+  if (root >= 0) {
+#pragma unroll
+    for (int af = 0; af < 2; ++af)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (16 * af + 4 * g + q < kMaxA) q0[(long long)root * kMaxA + 16 * af + 4 * g + q] = qv[af][q];
+  }
+}
+
 // fc2 after fc1_kernel<P, true>: Q[a] = (part_0[a] + part_1[a]) * scale
 // + b[a] (the two neuron halves in order); V = max over the stack's A
 // actions; a root item's q0 row.  Two stacks per wavefront, lane = action.
@@ -403,6 +602,22 @@ __global__ void fc1_weight_tiles_kernel(const unsigned char* __restrict__ src, u
       *reinterpret_cast<const uint4*>(src + sr * K * eb + kb);
 }
 
+// H of at most kFc1Medium stacks by the smaller tiles
+template <int P>
+void fc1_tiles(long long n, const unsigned char* X, const unsigned char* W, const float* bias, float acc_scale,
+               float out_s8, unsigned char* H, hipStream_t s) {
+  if (n <= kFc1Tiny) {
+    const dim3 grid((unsigned)((n + 31) / 32), 512 / 32);
+    hipLaunchKernelGGL((fc1_tile_kernel<P, 32, 32, 2, 1>), grid, dim3(128), 0, s, n, X, W, bias, acc_scale, out_s8, H);
+  } else if (n <= kFc1Small) {
+    const dim3 grid((unsigned)((n + 63) / 64), 512 / 64);
+    hipLaunchKernelGGL((fc1_tile_kernel<P, 64, 64, 2, 2>), grid, dim3(256), 0, s, n, X, W, bias, acc_scale, out_s8, H);
+  } else {
+    const dim3 grid((unsigned)((n + 127) / 128), 512 / 128);
+    hipLaunchKernelGGL((fc1_tile_kernel<P, 128, 128, 4, 2>), grid, dim3(512), 0, s, n, X, W, bias, acc_scale, out_s8, H);
+  }
+}
+
 }  // namespace
 
 void launch_fc1_weight_tiles(const void* src, void* dst, int N, int K, int eb, hipStream_t s) {
@@ -411,35 +626,66 @@ void launch_fc1_weight_tiles(const void* src, void* dst, int N, int K, int eb, h
                      reinterpret_cast<const unsigned char*>(src), reinterpret_cast<unsigned char*>(dst), N, K, eb);
 }
 
+namespace {
+// stacks of n that whole rounds of 256 x 256 tiles take (see kFc1Round)
+long long fc1_rounds(long long n) { return n % kFc1Round <= kFc1Medium ? n - n % kFc1Round : n; }
+
+dim3 fc1_grid(long long n) { return dim3((unsigned)(((n + kBM - 1) / kBM + 7) / 8 * 8 * (512 / kBN))); }
+
+template <int P>
+void fc1(long long n, const unsigned char* X, const unsigned char* W, const float* bias, float acc_scale, float out_s8,
+         unsigned char* H, hipStream_t s) {
+  constexpr int EB = FT<P>::EB;
+  const long long full = fc1_rounds(n);
+  if (full > 0)
+    hipLaunchKernelGGL(fc1_kernel<P>, fc1_grid(full), dim3(kThreads), 0, s, full, X, W, bias, acc_scale, out_s8, H,
+                       nullptr, nullptr);
+  if (full < n)
+    fc1_tiles<P>(n - full, X + fc1_tiled_offset(full, 0, EB), W, bias, acc_scale, out_s8, H + full * 512 * EB, s);
+}
+
+template <int P>
+void fc12(long long n, const unsigned char* X, const unsigned char* W1, const float* b1, float scale1, float out_s8,
+          const unsigned char* W2, unsigned char* part, hipStream_t s, hipEvent_t ev_after_fc1, const float* b2,
+          float scale2, const ItemDesc* desc, float* V, float* q0) {
+  constexpr int EB = FT<P>::EB;
+  const long long full = fc1_rounds(n);
+  float* sums = reinterpret_cast<float*>(part);
+  unsigned char* H = part + full * 512 * EB;
+  if (full > 0)
+    hipLaunchKernelGGL((fc1_kernel<P, true>), fc1_grid(full), dim3(kThreads), 0, s, full, X, W1, b1, scale1, out_s8,
+                       nullptr, W2, sums);
+  if (full < n) fc1_tiles<P>(n - full, X + fc1_tiled_offset(full, 0, EB), W1, b1, scale1, out_s8, H, s);
+  if (ev_after_fc1) (void)hipEventRecord(ev_after_fc1, s);
+  if (full > 0)
+    hipLaunchKernelGGL(fc2_sum_kernel, dim3((unsigned)((full + 7) / 8)), dim3(256), 0, s, full, sums, b2, scale2, desc, V,
+                       q0);
+  if (full < n)
+    hipLaunchKernelGGL(fc2_quarters_kernel<P>, dim3((unsigned)((n - full + 15) / 16)), dim3(256), 0, s, n - full, H, W2,
+                       b2, scale2, desc + full, V + full, q0);
+}
+}  // namespace
+
 void launch_fc1_mfma(int prec, long long n, const void* x3, const void* w, const float* bias, float acc_scale,
                      float out_s8, void* h, hipStream_t s) {
   if (n <= 0) return;
-  const long long mtiles = ((n + kBM - 1) / kBM + 7) / 8 * 8;
-  dim3 grid((unsigned)(mtiles * (512 / kBN))), block(kThreads);
   const unsigned char* X = reinterpret_cast<const unsigned char*>(x3);
-  const unsigned char* Wp = reinterpret_cast<const unsigned char*>(w);
+  const unsigned char* W = reinterpret_cast<const unsigned char*>(w);
   unsigned char* H = reinterpret_cast<unsigned char*>(h);
-  if (prec == P_BF16)
-    hipLaunchKernelGGL((fc1_kernel<P_BF16>), grid, block, 0, s, n, X, Wp, bias, acc_scale, out_s8, H, nullptr, nullptr);
-  else
-    hipLaunchKernelGGL((fc1_kernel<P_FP8>), grid, block, 0, s, n, X, Wp, bias, acc_scale, out_s8, H, nullptr, nullptr);
+  if (prec == P_BF16) fc1<P_BF16>(n, X, W, bias, acc_scale, out_s8, H, s);
+  else fc1<P_FP8>(n, X, W, bias, acc_scale, out_s8, H, s);
 }
 
 void launch_fc12(int prec, long long n, const void* x3, const void* w1, const float* b1, float scale1, float out_s8,
                  const void* w2, float* part, hipStream_t s, hipEvent_t ev_after_fc1, const float* b2, float scale2,
                  const ItemDesc* desc, float* V, float* q0) {
   if (n <= 0) return;
-  const long long mtiles = ((n + kBM - 1) / kBM + 7) / 8 * 8;
-  dim3 grid((unsigned)(mtiles * (512 / kBN))), block(kThreads);
   const unsigned char* X = reinterpret_cast<const unsigned char*>(x3);
   const unsigned char* W1 = reinterpret_cast<const unsigned char*>(w1);
   const unsigned char* W2 = reinterpret_cast<const unsigned char*>(w2);
-  if (prec == P_BF16)
-    hipLaunchKernelGGL((fc1_kernel<P_BF16, true>), grid, block, 0, s, n, X, W1, b1, scale1, out_s8, nullptr, W2, part);
-  else
-    hipLaunchKernelGGL((fc1_kernel<P_FP8, true>), grid, block, 0, s, n, X, W1, b1, scale1, out_s8, nullptr, W2, part);
-  if (ev_after_fc1) (void)hipEventRecord(ev_after_fc1, s);
-  hipLaunchKernelGGL(fc2_sum_kernel, dim3((unsigned)((n + 7) / 8)), dim3(256), 0, s, n, part, b2, scale2, desc, V, q0);
+  unsigned char* B = reinterpret_cast<unsigned char*>(part);
+  if (prec == P_BF16) fc12<P_BF16>(n, X, W1, b1, scale1, out_s8, W2, B, s, ev_after_fc1, b2, scale2, desc, V, q0);
+  else fc12<P_FP8>(n, X, W1, b1, scale1, out_s8, W2, B, s, ev_after_fc1, b2, scale2, desc, V, q0);
 }
 
 }  // namespace bcts

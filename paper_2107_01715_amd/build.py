@@ -14,8 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libbcts.so")
 BUILD = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "plan.cpp", "mlp_host.cpp", "expand.hip", "qnet.hip", "qnet_fused.hip", "qnet_siblings.hip",
-           "fc.hip", "backup.hip",
-           "mlp.hip"]
+           "qnet_split.hip", "fc.hip", "backup.hip", "mlp.hip"]
 ARCH = os.environ.get("BCTS_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CXX = os.environ.get("CXX", "g++")

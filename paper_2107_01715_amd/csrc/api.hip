@@ -358,6 +358,49 @@ bcts_status enqueue_level(bcts_ctx* c, const Plan& p, char* A, int k, const int3
   return BCTS_OK;
 }
 
+// Powers of two that bring the FP32 network's operands into FP16's range
+// (qnet_split.hip) and what they make of the accumulator scales and biases;
+// false when one is beyond 2^+-60 (weights or biases of a size no trained
+// network has), where the FP32 instruction runs.
+struct SplitScales {
+  std::vector<float> row[4], out[4], bias[4];
+};
+bool split_scales(const std::vector<float>* W, const std::vector<float>* B, SplitScales* sp) {
+  bool ok = true;
+  double bound = 255.0;          // of the layer's inputs, unscaled
+  int e_in = 0;                  // inputs are held times 2^e_in
+  for (int l = 0; l < 4; ++l) {
+    const size_t N = B[l].size(), K = W[l].size() / N;
+    const double acc = l == 0 ? 1.0 / 255.0 : 1.0;
+    std::vector<int> e_row(N, 0);
+    double top = 0.0;
+    for (size_t o = 0; o < N; ++o) {
+      double sum = 0.0, m = 0.0;
+      for (size_t k = 0; k < K; ++k) {
+        const double v = std::fabs((double)W[l][o * K + k]);
+        sum += v;
+        m = std::max(m, v);
+      }
+      top = std::max(top, sum * bound * acc + std::fabs((double)B[l][o]));
+      if (m > 0.0) e_row[o] = 13 - std::ilogb(m);
+    }
+    int e_out = 0;                // fc1's outputs stay FP32, unscaled
+    if (l < 3 && top > 0.0) e_out = 14 - std::ilogb(top);
+    ok = ok && std::abs(e_out) <= 60;
+    for (size_t o = 0; o < N; ++o) {
+      ok = ok && std::abs(e_row[o]) <= 60;
+      const int er = std::max(-60, std::min(60, e_row[o])), eo = std::max(-60, std::min(60, e_out));
+      sp->row[l].push_back((float)std::ldexp(1.0, er));
+      // conv1: 1/255 as the FP32 path multiplies it
+      sp->out[l].push_back((float)std::ldexp(l == 0 ? (double)(1.f / 255.f) : 1.0, eo - er - e_in));
+      sp->bias[l].push_back((float)std::ldexp((double)B[l][o], eo));
+    }
+    bound = top;
+    e_in = std::max(-60, std::min(60, e_out));
+  }
+  return ok;
+}
+
 // conv1 of a layer-path chunk by sibling groups (true) or stack by stack.
 // Workgroups of 128 pixel rows, about kSlots resident at once: the group
 // kernel runs 6 + 2 x (group size) stages per workgroup, the per-stack
@@ -387,7 +430,11 @@ bcts_status enqueue_qnet_chunk(bcts_ctx* c, const Plan& p, char* A, ItemDesc* de
   const long long cnt = ch.i1 - ch.i0;
   launch_item_desc(ch.i0, cnt, reinterpret_cast<const Seg*>(A + p.o_segs), (int)p.segs.size(), roots, fb, desc, s);
   if (!p.fused) {
-    const ChunkGroups cg{groups + ch.g0, conv1_by_groups(c, ch) ? ch.g1 - ch.g0 : 0, ch.i0};
+    if (c->prec == P_FP32 && c->q.split) {
+      launch_qnet_split(c->q, desc, cnt, ChunkGroups{groups + ch.g0, ch.g1 - ch.g0, ch.i0, ch.max_group}, ws, V + ch.i0, q0, s, cev);
+      return BCTS_OK;
+    }
+    const ChunkGroups cg{groups + ch.g0, conv1_by_groups(c, ch) ? ch.g1 - ch.g0 : 0, ch.i0, ch.max_group};
     launch_qnet_groups(c->prec, c->q, desc, cnt, cg, ws, V + ch.i0, q0, s, cev);
     return BCTS_OK;
   }
@@ -438,7 +485,11 @@ bcts_status enqueue_tail(bcts_ctx* c, const Plan& p, char* A, ItemDesc* desc, ch
   for (const auto& tc : p.tail_chunks) {
     const long long cnt = tc.i1 - tc.i0;
     launch_item_desc(tc.i0, cnt, reinterpret_cast<const Seg*>(A + p.o_segs), (int)p.segs.size(), roots, fb, desc, s);
-    const ChunkGroups cg{groups + tc.g0, conv1_by_groups(c, tc) ? tc.g1 - tc.g0 : 0, tc.i0};
+    if (c->q.split) {
+      launch_qnet_split(c->q, desc, cnt, ChunkGroups{groups + tc.g0, tc.g1 - tc.g0, tc.i0, tc.max_group}, ws, V + tc.i0, q0, s);
+      continue;
+    }
+    const ChunkGroups cg{groups + tc.g0, conv1_by_groups(c, tc) ? tc.g1 - tc.g0 : 0, tc.i0, tc.max_group};
     launch_qnet_groups(P_FP32, c->q, desc, cnt, cg, ws, V + tc.i0, q0, s, nullptr);
   }
   return BCTS_OK;
@@ -1144,6 +1195,14 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
     off[l][5] = o; o += (l == 1 || l == 2) ? align_up(n) : l == 3 ? align_up(fc1_tiles * fc1_tile_bytes(1)) : 0;
     off[l][6] = o; o += (l == 1 || l == 2) ? align_up(n) : 0;        // FP8 for the K = 128 instruction
   }
+  // the split planes: scales of rows and layers, then per layer planes, row scales, output scales, biases
+  SplitScales sp;
+  c->q.split = split_scales(W, B, &sp);
+  size_t soff[4][4];
+  for (int l = 0; l < 4; ++l) {
+    soff[l][0] = o; o += align_up(W[l].size() * 4);
+    for (int k = 1; k < 4; ++k) { soff[l][k] = o; o += align_up(B[l].size() * 4); }
+  }
   if (c->wmem) {
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     HIPCHECK(c, hipFree(c->wmem));
@@ -1180,6 +1239,16 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
       launch_fc1_weight_tiles(c->q.wb[l], const_cast<void*>(c->q.wfb[l]), NK[l][0], NK[l][1], 2, c->stream);
       launch_fc1_weight_tiles(c->q.w8[l], const_cast<void*>(c->q.wf8[l]), NK[l][0], NK[l][1], 1, c->stream);
     }
+  }
+  for (int l = 0; l < 4; ++l) {
+    const std::vector<float>* v[3] = {&sp.row[l], &sp.out[l], &sp.bias[l]};
+    for (int k = 0; k < 3; ++k)
+      HIPCHECK(c, hipMemcpy(base + soff[l][k + 1], v[k]->data(), v[k]->size() * 4, hipMemcpyHostToDevice));
+    launch_split_weights(c->q.w[l], reinterpret_cast<const float*>(base + soff[l][1]), NK[l][0], NK[l][1], l == 3,
+                         base + soff[l][0], c->stream);
+    c->q.wsplit[l] = base + soff[l][0];
+    c->q.ssplit[l] = reinterpret_cast<const float*>(base + soff[l][2]);
+    c->q.bsplit[l] = reinterpret_cast<const float*>(base + soff[l][3]);
   }
   // activation scales until calibrated: pixels 1:1 (255 -> 256 in e4m3), others unit
   c->q.ascale[0] = 1.f;

@@ -90,6 +90,13 @@ struct QnetDev {
   const void* wfb[5];          // bf16
   const void* wf8[5];          // e4m3
   const void* wf8k[5];         // e4m3, conv2 / conv3 for the K = 128 instruction (launch_fragment_major_k128)
+  // conv1..fc1 as two FP16 planes each, rows scaled by powers of two (see
+  // launch_split_weights); layer output = ReLU(sum ssplit[o] + bsplit[o]),
+  // the conv layers' in the scale of their splits, fc1's in its own.
+  // split false: a scale is out of range, FP32 runs on the FP32 instruction.
+  bool split;
+  const void* wsplit[4];
+  const float *ssplit[4], *bsplit[4];
 };
 
 // Learned forward-model world: weights on the device, FP32.  The four layers
@@ -145,6 +152,20 @@ void launch_fragment_major(const void* src, void* dst, int N, int K, int eb, boo
 // K % 128 remainder; rows paired as above.
 void launch_fragment_major_k128(const void* src, void* dst, int N, int K, hipStream_t s);
 
+// conv1 -> conv2 -> conv3 in split FP16 (see qnet_split.hip).
+constexpr long long kSplitRow = kFc1K / 32 * 128;      // bytes of a stack's x3, a neuron's fc1 weights
+struct SplitConvArgs {
+  const FusedGroup* groups;    // null: stack by stack
+  long long item_base;
+  const ItemDesc* desc;
+  long long n_groups, units;   // groups (stacks), groups x the runs the largest is cut into
+  int per_run;                 // stacks a run
+  const void* w[3];
+  const float *scale[3], *bias[3];
+  unsigned char* x3;           // [stacks][98][2][32] FP16
+};
+void launch_split_weights(const float* w, const float* row_scale, int N, int K, bool rows, void* out, hipStream_t s);
+
 // Copies fc1's W[N][K] (N a multiple of 256, eb bytes per element) into
 // stage-major tiles.
 void launch_fc1_weight_tiles(const void* src, void* dst, int N, int K, int eb, hipStream_t s);
@@ -157,13 +178,15 @@ void launch_fc1_mfma(int prec, long long n, const void* x3, const void* w, const
 
 // fc1 with fc2 folded into its epilogue (BF16 / FP8; w2 [32][512] in the
 // operand type, bias b2, accumulator scale scale2): fc2 takes the fc1
-// outputs rounded to the operand type, as launch_fc1_mfma stores them; each
-// fc1 workgroup sums fc2 over its 256 neurons into part [2][n][32] FP32 (256
-// bytes per stack, device memory the caller owns), then a second kernel adds
-// the two halves in order and writes V[item] = max over the item's A actions
-// and the q0 rows of root items.  The sum over the 512 neurons is associated
-// as (0..127 + 128..255) + (256..383 + 384..511).  With ev_after_fc1 an event
-// is recorded between the two launches.
+// outputs rounded to the operand type, as launch_fc1_mfma stores them; an
+// fc1 workgroup of 256 x 256 sums fc2 over its 256 neurons into part [2][n][32]
+// FP32, then a second kernel adds the two halves in order and writes V[item] =
+// max over the item's A actions and the q0 rows of root items; the stacks of
+// smaller tiles leave fc1's outputs in part, [n][512] in the operand type, and
+// the second kernel sums them.  Either way the sum over the 512 neurons is
+// associated as (0..127 + 128..255) + (256..383 + 384..511).  part: 512
+// elements of the operand type per stack, device memory the caller owns.  With
+// ev_after_fc1 an event is recorded between fc1 and fc2.
 void launch_fc12(int prec, long long n, const void* x3, const void* w1, const float* b1, float scale1, float out_s8,
                  const void* w2, float* part, hipStream_t s, hipEvent_t ev_after_fc1, const float* b2, float scale2,
                  const ItemDesc* desc, float* V, float* q0);

@@ -870,7 +870,7 @@ void launch_item_desc(long long item_begin, long long n_items, const Seg* segs, 
 
 void launch_qnet(int prec, const QnetDev& q, const ItemDesc* desc, long long n, void* ws, float* V,
                  float* q0, hipStream_t s, hipEvent_t* ev) {
-  launch_qnet_groups(prec, q, desc, n, ChunkGroups{nullptr, 0, 0}, ws, V, q0, s, ev);
+  launch_qnet_groups(prec, q, desc, n, ChunkGroups{nullptr, 0, 0, 1}, ws, V, q0, s, ev);
 }
 
 void launch_qnet_groups(int prec, const QnetDev& q, const ItemDesc* desc, long long n, const ChunkGroups& cg,

@@ -10,6 +10,7 @@ struct ChunkGroups {
   const FusedGroup* groups;
   int n;
   long long item_base;
+  int max_group;               // stacks in the largest group
 };
 
 // launch_qnet, with conv1 computing the channels a group's stacks share
@@ -17,5 +18,11 @@ struct ChunkGroups {
 // runs conv1 stack by stack, as launch_qnet does.
 void launch_qnet_groups(int prec, const QnetDev& q, const ItemDesc* desc, long long n_items, const ChunkGroups& cg,
                         void* ws, float* V, float* q0, hipStream_t s, hipEvent_t* ev = nullptr);
+
+// The FP32 network in split FP16 (q.split), conv1's shared channels once per
+// run of a group's stacks.  A stack's results do not depend on the others, nor
+// on cg.  The events bracket the conv layers (1..3 at once), fc1 and fc2.
+void launch_qnet_split(const QnetDev& q, const ItemDesc* desc, long long n_items, const ChunkGroups& cg, void* ws,
+                       float* V, float* q0, hipStream_t s, hipEvent_t* ev = nullptr);
 
 }  // namespace bcts

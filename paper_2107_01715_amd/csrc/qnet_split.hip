@@ -11,7 +11,7 @@
 // bits 2.0e-7 of the largest Q over 256 searches of A = 6, d = 3 (2.8e-7 on the
 // FP32 instruction), 1.1e-6 for one search (1.7e-6).
 //
-// Time, 256 searches of A = 6, d = 3 (57,088 stacks): conv layers 2.29 ms where
+// Time, 256 searches of A = 6, d = 3 (57,088 stacks): conv layers 2.23 ms where
 // layer-by-layer kernels on v_mfma_f32_16x16x4_f32 took 5.86 (the FP32
 // instruction alone 4.2 at the card's 154 TFLOP/s), fc1 0.56 (1.65).
 //
@@ -40,12 +40,12 @@ __device__ __forceinline__ f32x4 mma(h16x8 a, h16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ void split8(const float (&v)[8], h16x8& hi, h16x8& lo) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    hi[e] = (_Float16)v[e];
-    lo[e] = (_Float16)(v[e] - (float)hi[e]);
-  }
+// a, b as two FP16 pairs: hi, and what hi leaves of them (exact in FP32, one
+// instruction a value with its rounding to FP16)
+__device__ __forceinline__ void split2(float a, float b, unsigned& hi, unsigned& lo) {
+  hi = __builtin_bit_cast(unsigned, h16x2{(_Float16)a, (_Float16)b});
+  __asm__("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "v"(a));
+  __asm__("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "v"(b));
 }
 
 // ---- conv1 -> conv2 -> conv3 --------------------------------------------
@@ -111,13 +111,17 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[T][NF], const floa
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int m = (rg + RG * t) * 16 + r16;
-    typedef __attribute__((ext_vector_type(C))) _Float16 hv;
-    hv hi, lo;
+    __attribute__((ext_vector_type(C / 2))) unsigned hi, lo;
 #pragma unroll
-    for (int e = 0; e < C; ++e) {
-      const float v = fmaxf(fmaf(acc[t][e >> 2][e & 3], sc[e], b[e]), 0.f);
-      hi[e] = (_Float16)v;
-      lo[e] = (_Float16)(v - (float)hi[e]);
+    for (int e = 0; e < C; e += 2) {
+      float v[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        v[k] = fmaxf(fmaf(acc[t][(e + k) >> 2][(e + k) & 3], sc[e + k], b[e + k]), 0.f);
+      unsigned h, l;
+      split2(v[0], v[1], h, l);
+      hi[e / 2] = h;
+      lo[e / 2] = l;
     }
     if (m < M) st(m, ch >> 3, (ch & 7) * 2, hi, lo);
   }
@@ -147,13 +151,14 @@ __global__ void __launch_bounds__(512) conv_split_kernel(SplitConvArgs a) {
     if (sub >= end) continue;
 
     // conv1 over the shared channels: this wavefront's pixel tiles wave, wave + 8, ..
-    int pix[4];
+    int xo[4];
     unsigned off[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int p = (wave + 8 * t) * 16 + r16;
-      pix[t] = p < 400 ? p : 399;
-      off[t] = (pix[t] / 20 * 4 + g) * kFrame + pix[t] % 20 * 4;
+      const int y = (p < 400 ? p : 399) / 20, x = (p < 400 ? p : 399) % 20, q = y * 20 + (x >> 1) + 10 * (x & 1);
+      off[t] = (y * 4 + g) * kFrame + x * 4;
+      xo[t] = q * 128 + ((g ^ (q & 7)) << 4);
     }
     auto pixels = [&](const uint8_t* f, int t, int half) {
       const unsigned* q = reinterpret_cast<const unsigned*>(f + half * 4 * kFrame + off[t]);
@@ -252,12 +257,17 @@ __global__ void __launch_bounds__(512) conv_split_kernel(SplitConvArgs a) {
             float v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = fmaxf(fmaf(acc[t][e >> 2][e & 3], sc[e], b[e]), 0.f);
-            h16x8 hi, lo;
-            split8(v, hi, lo);
-            const int y = pix[t] / 20, x = pix[t] % 20, p = y * 20 + (x >> 1) + 10 * (x & 1);
-            const int o = i * kX1 + p * 128 + ((g ^ (p & 7)) << 4);
-            *reinterpret_cast<h16x8*>(x1 + o) = hi;
-            *reinterpret_cast<h16x8*>(x1 + (o ^ 64)) = lo;
+            u32x4 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              unsigned h, l;
+              split2(v[2 * e], v[2 * e + 1], h, l);
+              hi[e] = h;
+              lo[e] = l;
+            }
+            const int o = i * kX1 + xo[t];
+            *reinterpret_cast<u32x4*>(x1 + o) = hi;
+            *reinterpret_cast<u32x4*>(x1 + (o ^ 64)) = lo;
           }
         }
       }
@@ -279,13 +289,14 @@ __global__ void __launch_bounds__(512) conv_split_kernel(SplitConvArgs a) {
         for (int t = 0; t < T2; ++t)
 #pragma unroll
           for (int f = 0; f < NF; ++f) acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const unsigned lo16 = (unsigned)fresh((ng * NF * 128 + lane) * 16);
+        unsigned wo = (ng * NF * 128 + lane) * 16 - 8192;
         h16x8 w[3][NF][2];
         auto load_w = [&](int ks) {
+          wo = (unsigned)fresh((int)wo + 8192);
 #pragma unroll
           for (int f = 0; f < NF; ++f)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) w[ks % 3][f][pl] = ldw(a.w[1], (ks * 4 + f) * 2 + pl, lo16);
+            for (int pl = 0; pl < 2; ++pl) w[ks % 3][f][pl] = ldw(a.w[1], f * 2 + pl, wo);
         };
         h16x8 x[2][T2][2];
         auto load_x = [&](int ks) {
@@ -333,13 +344,14 @@ __global__ void __launch_bounds__(512) conv_split_kernel(SplitConvArgs a) {
         for (int t = 0; t < T3; ++t)
 #pragma unroll
           for (int f = 0; f < NF; ++f) acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const unsigned lo16 = (unsigned)fresh((ng * NF * 128 + lane) * 16);
+        unsigned wo = (ng * NF * 128 + lane) * 16 - 8192;
         h16x8 w[3][NF][2];
         auto load_w = [&](int ks) {
+          wo = (unsigned)fresh((int)wo + 8192);
 #pragma unroll
           for (int f = 0; f < NF; ++f)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) w[ks % 3][f][pl] = ldw(a.w[2], (ks * 4 + f) * 2 + pl, lo16);
+            for (int pl = 0; pl < 2; ++pl) w[ks % 3][f][pl] = ldw(a.w[2], f * 2 + pl, wo);
         };
         h16x8 x[2][T3][2];
         auto load_x = [&](int ks) {

@@ -503,7 +503,8 @@ bcts_status enqueue_backup(bcts_ctx* c, const Plan& p, char* A, float gamma, flo
   LevelRet lr{};
   for (int k = 1; k <= p.maxd; ++k) lr.ret[k] = reinterpret_cast<const float*>(A + p.o_ret[k]);
   launch_backup_correct(p.n, reinterpret_cast<const RootInfo*>(A + p.o_roots), reinterpret_cast<float*>(A + p.o_V),
-                        reinterpret_cast<float*>(A + p.o_q0), lr, gamma, corr_scale, d_act, d_q, s);
+                        reinterpret_cast<float*>(A + p.o_q0), lr, gamma, corr_scale,
+                        p.maxd > 0 ? p.lvl_count[p.maxd] / p.n : 0, d_act, d_q, s);
   return BCTS_OK;
 }
 

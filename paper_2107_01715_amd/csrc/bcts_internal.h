@@ -229,8 +229,9 @@ void launch_qnet(int prec, const QnetDev& q, const ItemDesc* desc, long long n_i
 struct LevelRet {
   const float* ret[kMaxD + 1];   // ret_k per level (index 0 unused)
 };
+// leaves: about a root's, for the launch's shape
 void launch_backup_correct(int n_roots, const RootInfo* roots, const float* V, const float* q0,
-                           const LevelRet& level_ret, float gamma, float corr_scale,
+                           const LevelRet& level_ret, float gamma, float corr_scale, long long leaves,
                            int* out_action, float* out_q, hipStream_t s);
 
 // fp32 -> bf16 / e4m3 conversion of weight arrays on the device

@@ -1,0 +1,42 @@
+"""A root's result does not depend on what is searched with it: levels of few
+and of many nodes expand, and roots of few and of many leaves back up, in
+launches of different shapes."""
+import numpy as np
+import pytest
+
+from paper_2107_01715_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+# (A, d) of the roots searched together, index of the one also searched alone
+BATCHES = [
+    ([(9, 3)] + [(2, 3)] * 20, 0),            # 729 leaves among roots of 8
+    ([(9, 3)] * 9, 8),                        # levels of 81 and 729 nodes, then 729 and 6,561
+    ([(18, 2)] * 13, 12),                     # 4,212 nodes at level 2, 324 alone
+    ([(4, 0), (18, 3), (3, 1)], 1),           # depth 0 among deeper ones
+]
+
+
+@pytest.mark.parametrize("shapes,which", BATCHES)
+def test_root_alone_and_in_a_batch(shapes, which):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_01715_amd import bcts as lib
+    ctx = lib.Context(0)
+    e = W.env_params(7)
+    ctx.set_env(e.delta, e.vel)
+    ctx.set_qnet(W.qnet_blob(W.qnet_weights(7)))
+    corr = lib.correction(True)
+    for prec in (lib.FP32, lib.BF16):
+        ctx.set_precision(prec)
+        pos, stacks = W.roots(31, len(shapes))
+        A = np.array([s[0] for s in shapes], np.int32)
+        d = np.array([s[1] for s in shapes], np.int32)
+        act, q = ctx.search_batch(pos, stacks, d, A, 0.99, corr)
+        one = slice(which, which + 1)
+        act1, q1 = ctx.search_batch(pos[one], stacks[one], d[one], A[one], 0.99, corr)
+        n = shapes[which][0]
+        assert act[which] == act1[0]
+        assert np.array_equal(q[which][:n], q1[0][:n])
+    ctx.close()

@@ -7,8 +7,10 @@
 // The stack is not replicated: a frame is written once, at the node that
 // renders it; Q-network inputs read the 4 ancestor frames in place.
 //
-// Work split: a 256-thread workgroup takes 8 nodes at a time.
-//   1. one thread per node: find the root, read the parent, move, score;
+// Work split: a 256-thread workgroup takes 8 nodes at a time, or one node
+// where a level has few (kFewNodes): then a level is one chain of loads, and
+// eight nodes a workgroup only make its passes longer.
+//   1. one thread per (node, sprite): find the root, read the parent, move, score;
 //   2. per (node, row): the row's coverage as two 84-bit masks (value 255
 //      from sprite 0, 128 from the others), kept in LDS;
 //   3. per (node, 16-byte chunk of the flat frame): expand the masks to
@@ -24,6 +26,10 @@ namespace bcts {
 namespace {
 
 constexpr int kNB = 8;                       // nodes per workgroup iteration
+// Levels of 18 and 324 nodes: 5.5 us each with one node a workgroup, 12.5 with
+// eight and a thread a node in step 1.  From 16 workgroups a CU the write
+// stream sets the time and the root search is better shared.
+constexpr long long kFewNodes = 4096;
 constexpr int kChunks = kFrameBytes / 16;    // 441 16-byte chunks per frame
 constexpr int kThreads = 256;
 
@@ -203,32 +209,74 @@ __global__ void __launch_bounds__(kThreads) move_kernel(LevelStep v, long long n
   if (node < n_nodes) step_node(v, node, p);
 }
 
+// step_node with a thread per (node, sprite): the eight lanes of a node hold
+// its sprites; x, y are left as the sprite's position.  All lanes of a
+// wavefront call it (node < 0: idle lanes).
+__device__ __forceinline__ int step_sprite(const LevelStep& v, long long node, int i, int& x, int& y) {
+  const int k = v.k;
+  int r = 0, rew = 0;
+  float pret = 0.f;
+  x = y = 0;
+  if (node >= 0) {
+    const int e = find_root(v.lr, node);
+    r = v.lr.root[e];
+    const long long j = node - v.lr.start[e];
+    const RootInfo& ri = v.roots[r];
+    const int A = ri.A, a = (int)(j % A);
+    if (k == 1) {
+      const int* rp = v.root_pos + ((long long)r * kSprites + i) * 2;
+      x = wrap84(rp[0]);
+      y = wrap84(rp[1]);
+    } else {
+      const long long kb = ri.kbase[k - 1], pn = ri.base[k - 1] + (kb >= 0 ? (long long)v.prev_keep[kb + j / A] : j / A);
+      const unsigned w = *reinterpret_cast<const uint16_t*>(v.prev_pos + pn * 16 + 2 * i);
+      x = w & 255u;
+      y = w >> 8;
+      pret = v.prev_ret[pn];
+    }
+    x = wrap84(x + (i == 0 ? v.env.delta[a][0] : v.env.vel[i - 1][0]));
+    y = wrap84(y + (i == 0 ? v.env.delta[a][1] : v.env.vel[i - 1][1]));
+  }
+  const int l0 = (threadIdx.x & 63) & ~7;
+  int dx = wrap84(__shfl(x, l0) - x), dy = wrap84(__shfl(y, l0) - y);
+  dx = dx < kFrame - dx ? dx : kFrame - dx;
+  dy = dy < kFrame - dy ? dy : kFrame - dy;
+  const unsigned long long hits = __ballot(i > 0 && dx < 6 && dy < 6);
+  rew = __popc((unsigned)(hits >> l0) & 255u);
+  if (node >= 0) {
+    *reinterpret_cast<uint16_t*>(v.pos + node * 16 + 2 * i) = (uint16_t)(x | (y << 8));
+    if (i == 0) {
+      v.ret[node] = fmaf(v.gamma_pow, (float)rew, pret);   // one rounding (a beam ranks these)
+      v.rew[node] = (uint8_t)rew;
+    }
+  }
+  return r;
+}
+
+template <int NB>
 __global__ void __launch_bounds__(kThreads)
 expand_kernel(LevelStep v, long long n_nodes, int leaf_frames, uint8_t* __restrict__ frames) {
-  __shared__ int s_pos[kNB][kSprites][2];
-  __shared__ RowMask s_rows[kNB][kFrame];
-  __shared__ unsigned long long s_clo[kNB][kSprites];
-  __shared__ unsigned s_chi[kNB][kSprites];
-  __shared__ int s_draw[kNB];
+  __shared__ int s_y[NB][kSprites];
+  __shared__ RowMask s_rows[NB][kFrame];
+  __shared__ unsigned long long s_clo[NB][kSprites];
+  __shared__ unsigned s_chi[NB][kSprites];
+  __shared__ int s_draw[NB];
+  static_assert(NB * kSprites <= 64, "a group's sprites are one wavefront");
 
   const int tid = threadIdx.x;
-  for (long long g0 = (long long)blockIdx.x * kNB; g0 < n_nodes; g0 += (long long)gridDim.x * kNB) {
-    const int nb = (int)((n_nodes - g0) < kNB ? (n_nodes - g0) : kNB);
+  for (long long g0 = (long long)blockIdx.x * NB; g0 < n_nodes; g0 += (long long)gridDim.x * NB) {
+    const int nb = (int)((n_nodes - g0) < NB ? (n_nodes - g0) : NB);
 
-    // 1. move and score, one thread per node
-    if (tid < nb) {
-      int p[kSprites][2];
-      const int r = step_node(v, g0 + tid, p);
-      s_draw[tid] = leaf_frames || v.roots[r].d != v.k;
-      for (int i = 0; i < kSprites; ++i) {
-        s_pos[tid][i][0] = p[i][0];
-        s_pos[tid][i][1] = p[i][1];
-      }
-    }
-    __syncthreads();
-    if (tid < nb * kSprites) {
+    // 1. move and score, one thread per sprite
+    if (tid < 64) {
       const int b = tid / kSprites, i = tid % kSprites;
-      col_mask(s_pos[b][i][0], s_clo[b][i], s_chi[b][i]);
+      int x, y;
+      const int r = step_sprite(v, b < nb ? g0 + b : -1, i, x, y);
+      if (b < nb) {
+        s_y[b][i] = y;
+        col_mask(x, s_clo[b][i], s_chi[b][i]);
+        if (i == 0) s_draw[b] = leaf_frames || v.roots[r].d != v.k;
+      }
     }
     __syncthreads();
 
@@ -237,7 +285,8 @@ expand_kernel(LevelStep v, long long n_nodes, int leaf_frames, uint8_t* __restri
       const int b = t / kFrame, y = t % kFrame;
       RowMask m = {0ull, 0ull, 0u, 0u};
       for (int i = 0; i < kSprites; ++i) {
-        if (wrap84(y - s_pos[b][i][1]) < 6) {
+        const int dy = y - s_y[b][i];
+        if ((dy < 0 ? dy + kFrame : dy) < 6) {
           if (i == 0) { m.lo255 |= s_clo[b][i]; m.hi255 |= s_chi[b][i]; }
           else        { m.lo128 |= s_clo[b][i]; m.hi128 |= s_chi[b][i]; }
         }
@@ -289,9 +338,11 @@ void launch_expand(int k, long long n_nodes, LevelRoots lr, const RootInfo* root
   // shape: capping the grid at 65,536 workgroups that loop over several
   // groups, or marking the frame stores non-temporal, each slows the
   // level's HBM write stream (the three levels take 8% longer with both).
-  long long groups = (n_nodes + kNB - 1) / kNB;
-  int grid = (int)(groups < (1 << 20) ? groups : (1 << 20));
-  hipLaunchKernelGGL(expand_kernel, dim3(grid), dim3(kThreads), 0, s, v, n_nodes, leaf_frames ? 1 : 0, frames);
+  const int nb = n_nodes <= kFewNodes ? 1 : kNB;
+  const long long groups = (n_nodes + nb - 1) / nb;
+  const dim3 grid((unsigned)(groups < (1 << 20) ? groups : (1 << 20)));
+  if (nb == 1) hipLaunchKernelGGL(expand_kernel<1>, grid, dim3(kThreads), 0, s, v, n_nodes, leaf_frames ? 1 : 0, frames);
+  else hipLaunchKernelGGL(expand_kernel<kNB>, grid, dim3(kThreads), 0, s, v, n_nodes, leaf_frames ? 1 : 0, frames);
 }
 
 void launch_prune(int k, int n_level_roots, LevelRoots lr, const RootInfo* roots, const float* ret_k, int* keep_k,

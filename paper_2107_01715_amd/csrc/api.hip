@@ -335,26 +335,36 @@ FrameBases frame_bases(const bcts_ctx* c, const Plan& p, char* A, const uint8_t*
   return fb;
 }
 
-// Level k of the expansion (and its beam cut).
+// Level k of the expansion (and its beam cut).  A level that every root cuts
+// to half its nodes or less gets its frames after the cut, the kept nodes'
+// alone (all_frames: every node's): 331,776 nodes cut to 18,432 take 437 us
+// with all frames, 54 with the kept ones (move 21, frames 33).
 bcts_status enqueue_level(bcts_ctx* c, const Plan& p, char* A, int k, const int32_t* d_pos, float gamma,
-                          hipStream_t s) {
+                          hipStream_t s, bool all_frames = false) {
   bcts_status st = launch_gate(c);
   if (st != BCTS_OK) return st;
   const RootInfo* roots = reinterpret_cast<const RootInfo*>(A + p.o_roots);
   const float g = discount_f32(gamma, k - 1);    // the FP32 discount a pruned search ranks by
   LevelRoots lr{reinterpret_cast<const int*>(A + p.o_lroot[k]), reinterpret_cast<const long long*>(A + p.o_lstart[k]),
                 (int)p.lvl_root[k].size()};
-  bool inner = false;
-  for (int r : p.lvl_root[k]) inner = inner || p.roots[r].d > k;
+  bool inner = false, late = !all_frames && 2 * p.keep_count[k] <= p.lvl_count[k];
+  for (int r : p.lvl_root[k]) {
+    inner = inner || p.roots[r].d > k;
+    late = late && p.roots[r].kbase[k] >= 0;
+  }
+  uint8_t* frames = reinterpret_cast<uint8_t*>(A + p.o_frames[k]);
   launch_expand(k, p.lvl_count[k], lr, roots, d_pos,
                 k > 1 ? reinterpret_cast<const uint8_t*>(A + p.o_pos[k - 1]) : nullptr,
                 k > 1 ? reinterpret_cast<const float*>(A + p.o_ret[k - 1]) : nullptr,
                 k > 1 && p.keep_count[k - 1] > 0 ? reinterpret_cast<const int*>(A + p.o_keep[k - 1]) : nullptr,
-                c->env, g, !leaf_positions(c, p) || k < 2, inner, reinterpret_cast<uint8_t*>(A + p.o_pos[k]), reinterpret_cast<uint8_t*>(A + p.o_frames[k]),
-                reinterpret_cast<float*>(A + p.o_ret[k]), reinterpret_cast<uint8_t*>(A + p.o_rew[k]), s);
+                c->env, g, !late && (!leaf_positions(c, p) || k < 2), !late && inner,
+                reinterpret_cast<uint8_t*>(A + p.o_pos[k]), frames, reinterpret_cast<float*>(A + p.o_ret[k]), reinterpret_cast<uint8_t*>(A + p.o_rew[k]), s);
   if (p.keep_count[k] > 0)
     launch_prune(k, (int)p.lvl_root[k].size(), lr, roots, reinterpret_cast<const float*>(A + p.o_ret[k]),
                  reinterpret_cast<int*>(A + p.o_keep[k]), p.beam, s);
+  if (late)
+    launch_render_kept(k, p.keep_count[k], lr, roots, reinterpret_cast<const int*>(A + p.o_keep[k]),
+                       reinterpret_cast<uint8_t*>(A + p.o_pos[k]), frames, s);
   return BCTS_OK;
 }
 
@@ -1642,8 +1652,8 @@ bcts_status bcts_debug_expand_batch(bcts_ctx* c, int32_t n, const int32_t* pos, 
   HIPCHECK(c, hipMemcpyAsync(c->arena + p.o_root_pos, pos, sizeof(int32_t) * n * kSprites * 2, hipMemcpyHostToDevice,
                              s));
   for (int k = 1; k <= p.maxd; ++k)
-    if ((st = enqueue_level(c, p, c->arena, k, reinterpret_cast<const int32_t*>(c->arena + p.o_root_pos), gamma, s)) !=
-        BCTS_OK)
+    if ((st = enqueue_level(c, p, c->arena, k, reinterpret_cast<const int32_t*>(c->arena + p.o_root_pos), gamma, s,
+                            true)) != BCTS_OK)
       return st;
   HIPCHECK(c, hipGetLastError());
   HIPCHECK(c, hipStreamSynchronize(s));

@@ -209,6 +209,11 @@ void launch_expand(int k, long long n_nodes, LevelRoots lr, const RootInfo* root
                    const EnvTables& env, float gamma_pow, bool leaf_frames, bool any_inner, uint8_t* pos,
                    uint8_t* frames, float* ret, uint8_t* rew, hipStream_t s);
 
+// The frames of a level's kept nodes (n_kept entries of `keep`), after its
+// move and its cut; every root of the level must be cut there.
+void launch_render_kept(int k, long long n_kept, LevelRoots lr, const RootInfo* roots, const int* keep, uint8_t* pos,
+                        uint8_t* frames, hipStream_t s);
+
 // Beam cut of level k: for every root whose level k is cut and every root
 // action a0, the `beam` nodes of a0's block with the largest return (lowest
 // index on ties) go, ascending, to keep[kbase + a0 * beam ..].

@@ -253,14 +253,18 @@ __device__ __forceinline__ int step_sprite(const LevelStep& v, long long node, i
   return r;
 }
 
-template <int NB>
+// KEPT: the frames of the n_nodes entries of the level's keep list, the level
+// having been moved and cut before (every root of it: v.roots' kbase ascend).
+template <int NB, bool KEPT>
 __global__ void __launch_bounds__(kThreads)
-expand_kernel(LevelStep v, long long n_nodes, int leaf_frames, uint8_t* __restrict__ frames) {
+expand_kernel(LevelStep v, long long n_nodes, int leaf_frames, const int* __restrict__ keep,
+              uint8_t* __restrict__ frames) {
   __shared__ int s_y[NB][kSprites];
   __shared__ RowMask s_rows[NB][kFrame];
   __shared__ unsigned long long s_clo[NB][kSprites];
   __shared__ unsigned s_chi[NB][kSprites];
   __shared__ int s_draw[NB];
+  __shared__ long long s_node[NB];
   static_assert(NB * kSprites <= 64, "a group's sprites are one wavefront");
 
   const int tid = threadIdx.x;
@@ -270,12 +274,32 @@ expand_kernel(LevelStep v, long long n_nodes, int leaf_frames, uint8_t* __restri
     // 1. move and score, one thread per sprite
     if (tid < 64) {
       const int b = tid / kSprites, i = tid % kSprites;
-      int x, y;
-      const int r = step_sprite(v, b < nb ? g0 + b : -1, i, x, y);
+      long long node = b < nb ? g0 + b : -1;
+      int x = 0, y = 0;
+      bool draw = true;
+      if constexpr (KEPT) {
+        if (node >= 0) {
+          int lo = 0, hi = v.lr.cnt - 1;
+          while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (v.roots[v.lr.root[mid]].kbase[v.k] <= node) lo = mid; else hi = mid - 1;
+          }
+          node = v.lr.start[lo] + keep[node];
+          const unsigned w = *reinterpret_cast<const uint16_t*>(v.pos + node * 16 + 2 * i);
+          x = w & 255u;
+          y = w >> 8;
+        }
+      } else {
+        const int r = step_sprite(v, node, i, x, y);
+        draw = leaf_frames || v.roots[r].d != v.k;
+      }
       if (b < nb) {
         s_y[b][i] = y;
         col_mask(x, s_clo[b][i], s_chi[b][i]);
-        if (i == 0) s_draw[b] = leaf_frames || v.roots[r].d != v.k;
+        if (i == 0) {
+          s_draw[b] = draw;
+          s_node[b] = node;
+        }
       }
     }
     __syncthreads();
@@ -314,10 +338,21 @@ expand_kernel(LevelStep v, long long n_nodes, int leaf_frames, uint8_t* __restri
       v.y = pix4(m255 >> 4, m128 >> 4);
       v.z = pix4(m255 >> 8, m128 >> 8);
       v.w = pix4(m255 >> 12, m128 >> 12);
-      *reinterpret_cast<uint4*>(frames + (g0 + b) * kFrameBytes + o) = v;
+      *reinterpret_cast<uint4*>(frames + s_node[b] * kFrameBytes + o) = v;
     }
     __syncthreads();
   }
+}
+
+template <bool KEPT>
+void launch_render(const LevelStep& v, long long n, bool leaf_frames, const int* keep, uint8_t* frames, hipStream_t s) {
+  const int nb = n <= kFewNodes ? 1 : kNB;
+  const long long groups = (n + nb - 1) / nb;
+  const dim3 grid((unsigned)(groups < (1 << 20) ? groups : (1 << 20)));
+  if (nb == 1)
+    hipLaunchKernelGGL((expand_kernel<1, KEPT>), grid, dim3(kThreads), 0, s, v, n, leaf_frames ? 1 : 0, keep, frames);
+  else
+    hipLaunchKernelGGL((expand_kernel<kNB, KEPT>), grid, dim3(kThreads), 0, s, v, n, leaf_frames ? 1 : 0, keep, frames);
 }
 
 }  // namespace
@@ -338,11 +373,18 @@ void launch_expand(int k, long long n_nodes, LevelRoots lr, const RootInfo* root
   // shape: capping the grid at 65,536 workgroups that loop over several
   // groups, or marking the frame stores non-temporal, each slows the
   // level's HBM write stream (the three levels take 8% longer with both).
-  const int nb = n_nodes <= kFewNodes ? 1 : kNB;
-  const long long groups = (n_nodes + nb - 1) / nb;
-  const dim3 grid((unsigned)(groups < (1 << 20) ? groups : (1 << 20)));
-  if (nb == 1) hipLaunchKernelGGL(expand_kernel<1>, grid, dim3(kThreads), 0, s, v, n_nodes, leaf_frames ? 1 : 0, frames);
-  else hipLaunchKernelGGL(expand_kernel<kNB>, grid, dim3(kThreads), 0, s, v, n_nodes, leaf_frames ? 1 : 0, frames);
+  launch_render<false>(v, n_nodes, leaf_frames, nullptr, frames, s);
+}
+
+void launch_render_kept(int k, long long n_kept, LevelRoots lr, const RootInfo* roots, const int* keep, uint8_t* pos,
+                        uint8_t* frames, hipStream_t s) {
+  if (n_kept <= 0) return;
+  LevelStep v{};
+  v.k = k;
+  v.lr = lr;
+  v.roots = roots;
+  v.pos = pos;
+  launch_render<true>(v, n_kept, true, keep, frames, s);
 }
 
 void launch_prune(int k, int n_level_roots, LevelRoots lr, const RootInfo* roots, const float* ret_k, int* keep_k,

@@ -244,9 +244,8 @@ void plan_search(bcts_ctx* c, Plan& p, int n, const int32_t* depth, const int32_
             c->beam, c->corr_fp32, c->chunk_items);
 }
 
-// Copy the plan's tables to `arena` through the pinned staging buffer `h`
-// (at least p.table_bytes; the caller makes sure no earlier copy still reads it).
-bcts_status upload_tables_at(bcts_ctx* c, const Plan& p, char* arena, char* h, hipStream_t s) {
+// The plan's tables at their offsets in `h` (at least p.table_bytes).
+void stage_tables(const Plan& p, char* h) {
   std::memcpy(h + p.o_roots, p.roots.data(), sizeof(RootInfo) * p.n);
   std::memcpy(h + p.o_segs, p.segs.data(), sizeof(Seg) * p.segs.size());
   std::memcpy(h + p.o_groups, p.groups.data(), sizeof(FusedGroup) * p.groups.size());
@@ -254,6 +253,12 @@ bcts_status upload_tables_at(bcts_ctx* c, const Plan& p, char* arena, char* h, h
     std::memcpy(h + p.o_lroot[k], p.lvl_root[k].data(), sizeof(int) * p.lvl_root[k].size());
     std::memcpy(h + p.o_lstart[k], p.lvl_start[k].data(), sizeof(long long) * p.lvl_start[k].size());
   }
+}
+
+// Copy the plan's tables to `arena` through the pinned staging buffer `h`
+// (the caller makes sure no earlier copy still reads it).
+bcts_status upload_tables_at(bcts_ctx* c, const Plan& p, char* arena, char* h, hipStream_t s) {
+  stage_tables(p, h);
   HIPCHECK(c, hipMemcpyAsync(arena, h, p.table_bytes, hipMemcpyHostToDevice, s));
   return BCTS_OK;
 }
@@ -615,7 +620,12 @@ bcts_status collect_timing(bcts_ctx* c) {
   return BCTS_OK;
 }
 
-// Host-buffer search: stage inputs, run, copy results back.
+// Host-buffer search: stage inputs, run, copy results back.  Inputs of up to
+// kStagedInput bytes (36 roots) go through pinned memory in one copy: one
+// search of 4 actions, d = 1, 169 us with the tables, positions, stacks,
+// actions and Q-values copied one by one, 106 so; larger ones are copied
+// from where they are.
+constexpr size_t kStagedInput = (size_t)1 << 20;
 bcts_status search_host(bcts_ctx* c, int n, const int32_t* pos, const uint8_t* stacks, const int32_t* depth,
                         const int32_t* Av, float gamma, const bcts_correction& corr, int32_t* out_action,
                         float* out_q, int q_stride) {
@@ -624,6 +634,29 @@ bcts_status search_host(bcts_ctx* c, int n, const int32_t* pos, const uint8_t* s
   bcts_status st = ensure_arena(c, p.total);
   if (st != BCTS_OK) return st;
   hipStream_t s = c->stream;
+  if (p.o_act <= kStagedInput) {
+    // tables, positions and stacks are one range of the arena: one copy out of
+    // pinned memory, and the backup writes its results there itself
+    if ((st = order_arena(c, s)) != BCTS_OK) return st;
+    if ((st = ensure_pinned(c, p.o_q + sizeof(float) * (size_t)n * q_stride)) != BCTS_OK) return st;
+    HIPCHECK(c, hipStreamSynchronize(s));
+    char* h = c->pinned;
+    stage_tables(p, h);
+    std::memcpy(h + p.o_root_pos, pos, sizeof(int32_t) * n * kSprites * 2);
+    std::memcpy(h + p.o_root_stack, stacks, (size_t)n * 4 * kFrameBytes);
+    HIPCHECK(c, hipMemcpyAsync(c->arena, h, p.o_act, hipMemcpyHostToDevice, s));
+    int32_t* act = reinterpret_cast<int32_t*>(h + p.o_act);
+    float* q = reinterpret_cast<float*>(h + p.o_q);
+    st = enqueue_search(c, p, reinterpret_cast<const int32_t*>(c->arena + p.o_root_pos),
+                        reinterpret_cast<const uint8_t*>(c->arena + p.o_root_stack), gamma,
+                        corr.enabled ? corr.scale : 0.f, act, q, s, c->timing);
+    if (st != BCTS_OK) return st;
+    HIPCHECK(c, hipStreamSynchronize(s));
+    std::memcpy(out_action, act, sizeof(int32_t) * n);
+    std::memcpy(out_q, q, sizeof(float) * (size_t)n * q_stride);
+    c->arena_pending = false;
+    return c->timing ? collect_timing(c) : BCTS_OK;
+  }
   st = upload_tables(c, p, s);
   if (st != BCTS_OK) return st;
   const size_t in_bytes = sizeof(int32_t) * n * kSprites * 2 + (size_t)n * 4 * kFrameBytes;
@@ -697,7 +730,6 @@ struct Cohort {
   bcts_correction corr{};
   Plan p;
   size_t dev_off = 0, pin_off = 0, pin_bytes = 0;
-  size_t h_pos = 0, h_stack = 0, h_act = 0, h_q = 0;   // offsets inside its pinned range
   int n_stages = 0, next = 0;     // stages: levels 1..maxd, chunks, FP32 tail (if any), backup
   bool light = false;             // all stages in one step
   uint64_t last_step = 0;         // step holding its last stage (valid once next == n_stages)
@@ -833,8 +865,8 @@ struct ServeEngine {
     for (auto it = active.begin(); it != active.end();) {
       Cohort& k = *it;
       if (k.next < k.n_stages || k.last_step > done_step) { ++it; continue; }
-      const int32_t* act = reinterpret_cast<const int32_t*>(pinned + k.pin_off + k.h_act);
-      const float* q = reinterpret_cast<const float*>(pinned + k.pin_off + k.h_q);
+      const int32_t* act = reinterpret_cast<const int32_t*>(pinned + k.pin_off + k.p.o_act);
+      const float* q = reinterpret_cast<const float*>(pinned + k.pin_off + k.p.o_q);
       for (size_t i = 0; i < k.tickets.size(); ++i) {
         ServeResult r;
         r.action = act[i];
@@ -874,11 +906,8 @@ struct ServeEngine {
       Cohort k;
       make_plan(k.p, n, dep.data(), Av.data(), f.gamma, f.corr, kMaxA, chunk_items(), c->prec, true, fused(),
                 c->beam, c->corr_fp32, layer_chunk);
-      k.h_pos = align_up(k.p.table_bytes);
-      k.h_stack = k.h_pos + align_up(sizeof(int32_t) * n * kSprites * 2);
-      k.h_act = k.h_stack + align_up((size_t)n * 4 * kFrameBytes);
-      k.h_q = k.h_act + align_up(sizeof(int32_t) * n);
-      k.pin_bytes = k.h_q + align_up(sizeof(float) * (size_t)n * kMaxA);
+      // tables, inputs and results lie in the pinned range as they do in the arena
+      k.pin_bytes = align_up(k.p.o_q + sizeof(float) * (size_t)n * kMaxA);
       bool ok = pool.alloc(k.p.search_bytes(), &k.dev_off);
       if (ok && !pin_pool.alloc(k.pin_bytes, &k.pin_off)) {
         pool.release(k.dev_off, k.p.search_bytes());
@@ -892,15 +921,9 @@ struct ServeEngine {
       // stage the tables and inputs in the cohort's pinned range
       char* h = pinned + k.pin_off;
       const Plan& p = k.p;
-      std::memcpy(h + p.o_roots, p.roots.data(), sizeof(RootInfo) * p.n);
-      std::memcpy(h + p.o_segs, p.segs.data(), sizeof(Seg) * p.segs.size());
-      std::memcpy(h + p.o_groups, p.groups.data(), sizeof(FusedGroup) * p.groups.size());
-      for (int lv = 1; lv <= p.maxd; ++lv) {
-        std::memcpy(h + p.o_lroot[lv], p.lvl_root[lv].data(), sizeof(int) * p.lvl_root[lv].size());
-        std::memcpy(h + p.o_lstart[lv], p.lvl_start[lv].data(), sizeof(long long) * p.lvl_start[lv].size());
-      }
-      int32_t* hp = reinterpret_cast<int32_t*>(h + k.h_pos);
-      uint8_t* hs = reinterpret_cast<uint8_t*>(h + k.h_stack);
+      stage_tables(p, h);
+      int32_t* hp = reinterpret_cast<int32_t*>(h + p.o_root_pos);
+      uint8_t* hs = reinterpret_cast<uint8_t*>(h + p.o_root_stack);
       k.tickets.resize(n);
       k.A.resize(n);
       for (int i = 0; i < n; ++i) {
@@ -931,26 +954,15 @@ struct ServeEngine {
     char* ws = dev + align_up(sizeof(ItemDesc) * (size_t)std::max(chunk_items(), layer_chunk));
     const int32_t* d_pos = reinterpret_cast<const int32_t*>(A + p.o_root_pos);
     const uint8_t* d_stacks = reinterpret_cast<const uint8_t*>(A + p.o_root_stack);
-    const int n = p.n;
-    if (i == 0) {
-      HIPCHECK(c, hipMemcpyAsync(A, h, p.table_bytes, hipMemcpyHostToDevice, stream));
-      HIPCHECK(c, hipMemcpyAsync(A + p.o_root_pos, h + k.h_pos, sizeof(int32_t) * n * kSprites * 2,
-                                 hipMemcpyHostToDevice, stream));
-      HIPCHECK(c, hipMemcpyAsync(A + p.o_root_stack, h + k.h_stack, (size_t)n * 4 * kFrameBytes,
-                                 hipMemcpyHostToDevice, stream));
-    }
+    if (i == 0) HIPCHECK(c, hipMemcpyAsync(A, h, p.o_act, hipMemcpyHostToDevice, stream));
     const int nl = p.maxd, nc = (int)p.chunks.size(), nt = p.tail_chunks.empty() ? 0 : 1;
     if (i < nl) return enqueue_level(c, p, A, i + 1, d_pos, k.gamma, stream);
     const FrameBases fb = frame_bases(c, p, A, d_stacks);
     if (i < nl + nc) return enqueue_qnet_chunk(c, p, A, desc, ws, fb, i - nl, stream, nullptr);
     if (i < nl + nc + nt) return enqueue_tail(c, p, A, desc, ws, fb, stream);
-    int32_t* d_act = reinterpret_cast<int32_t*>(A + p.o_act);
-    float* d_q = reinterpret_cast<float*>(A + p.o_q);
-    bcts_status st = enqueue_backup(c, p, A, k.gamma, k.corr.enabled ? k.corr.scale : 0.f, d_act, d_q, stream);
-    if (st != BCTS_OK) return st;
-    HIPCHECK(c, hipMemcpyAsync(h + k.h_act, d_act, sizeof(int32_t) * n, hipMemcpyDeviceToHost, stream));
-    HIPCHECK(c, hipMemcpyAsync(h + k.h_q, d_q, sizeof(float) * (size_t)n * kMaxA, hipMemcpyDeviceToHost, stream));
-    return BCTS_OK;
+    // the results go straight to the cohort's pinned range
+    return enqueue_backup(c, p, A, k.gamma, k.corr.enabled ? k.corr.scale : 0.f,
+                          reinterpret_cast<int32_t*>(h + p.o_act), reinterpret_cast<float*>(h + p.o_q), stream);
   }
 
   // One step: admissions, then one stage of every cohort (all of a light

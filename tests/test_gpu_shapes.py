@@ -40,3 +40,24 @@ def test_root_alone_and_in_a_batch(shapes, which):
         assert act[which] == act1[0]
         assert np.array_equal(q[which][:n], q1[0][:n])
     ctx.close()
+
+
+def test_host_inputs_staged_and_direct():
+    """36 roots of 28 KB pass through pinned memory in one copy, 40 do not."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_01715_amd import bcts as lib
+    ctx = lib.Context(0)
+    e = W.env_params(7)
+    ctx.set_env(e.delta, e.vel)
+    ctx.set_qnet(W.qnet_blob(W.qnet_weights(7)))
+    ctx.set_precision(lib.BF16)
+    pos, stacks = W.roots(32, 40)
+    corr = lib.correction(True)
+    A, d = np.full(40, 4, np.int32), np.full(40, 2, np.int32)
+    act, q = ctx.search_batch(pos, stacks, d, A, 0.99, corr)
+    for n in (1, 36, 37):
+        act1, q1 = ctx.search_batch(pos[:n], stacks[:n], d[:n], A[:n], 0.99, corr)
+        assert np.array_equal(act1, act[:n]) and np.array_equal(q1, q[:n])
+    ctx.close()

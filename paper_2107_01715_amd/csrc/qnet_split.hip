@@ -496,10 +496,10 @@ fc1_split_kernel(long long n, const unsigned char* __restrict__ X, const unsigne
 
 // ---- fc2 ----------------------------------------------------------------
 // Q = h W2^T + b in FP32 (v_mfma_f32_16x16x4_f32), V = max over the stack's A
-// actions, the q0 rows of root items.  16 stacks a workgroup, an eighth of K a
+// actions, the q0 rows of root items.  IPB stacks a workgroup, an eighth of K a
 // wavefront, the eight sums added in pairs.  SLICES: H holds fc1's slices, of which h
-// is formed as fc1_split_kernel forms it.
-template <bool SLICES>
+// is formed as fc1_split_kernel forms it; 14 KB a stack, so few stacks a workgroup.
+template <bool SLICES, int IPB>
 __global__ void __launch_bounds__(512) fc2_split_kernel(long long n, const float* __restrict__ H,
                                                         const float* __restrict__ scale1, const float* __restrict__ bias1,
                                                         const float* __restrict__ W2, const float* __restrict__ bias,
@@ -507,7 +507,8 @@ __global__ void __launch_bounds__(512) fc2_split_kernel(long long n, const float
                                                         float* __restrict__ q0) {
   __shared__ f32x4 sums[8][2][64];
   const int lane = threadIdx.x & 63, c = threadIdx.x >> 6, r16 = lane & 15, g = lane >> 4;
-  const long long m = (long long)blockIdx.x * 16 + r16, mm = m < n ? m : n - 1;
+  const long long first = (long long)blockIdx.x * IPB, m = r16 < IPB ? first + r16 : n;
+  const long long mm = m < n ? m : first;
   const int A = desc[mm].A, root = desc[mm].q0_root;
   f32x4 h[4], w[2][4];
 #pragma unroll
@@ -613,7 +614,7 @@ void launch_split_weights(const float* w, const float* row_scale, int N, int K, 
 // 328 / 343.
 constexpr int kRunItems = 256, kPairItems = 256;
 // fc1 + fc2: K's slices as workgroups (32 x 32 tiles) up to kSplitFc1Small, 512
-// stacks 17 + 14 against 30 + 9 in 64 x 64 tiles, 1,024 26 + 14 / 31 + 8; then
+// stacks 17 + 10 against 30 + 9 in 64 x 64 tiles, 1,024 26 + 10 / 31 + 8; then
 // 64 x 64 tiles, and 256 x 128 ones for whole rounds of the chip (256 tiles,
 // kSplitFc1Round stacks) and for a rest past kSplitFc1Medium: 8,192 stacks 102
 // in 64 x 64 against 124 in 256 x 128, 14,336 143 / 132, 16,384 206 / 134;
@@ -665,12 +666,11 @@ void launch_qnet_split(const QnetDev& q, const ItemDesc* desc, long long n, cons
                          n - full, x3 + full * kSplitRow, w, q.ssplit[3], q.bsplit[3], h + full * 512, part);
   }
   if (ev) (void)hipEventRecord(ev[4], s);
-  const dim3 fgrid((unsigned)((n + 15) / 16));
   if (slices)
-    hipLaunchKernelGGL(fc2_split_kernel<true>, fgrid, dim3(512), 0, s, n, part, q.ssplit[3], q.bsplit[3], q.w[4], q.b[4],
+    hipLaunchKernelGGL((fc2_split_kernel<true, 4>), dim3((unsigned)((n + 3) / 4)), dim3(512), 0, s, n, part, q.ssplit[3], q.bsplit[3], q.w[4], q.b[4],
                        desc, V, q0);
   else
-    hipLaunchKernelGGL(fc2_split_kernel<false>, fgrid, dim3(512), 0, s, n, h, q.ssplit[3], q.bsplit[3], q.w[4], q.b[4],
+    hipLaunchKernelGGL((fc2_split_kernel<false, 16>), dim3((unsigned)((n + 15) / 16)), dim3(512), 0, s, n, h, q.ssplit[3], q.bsplit[3], q.w[4], q.b[4],
                        desc, V, q0);
   if (ev) (void)hipEventRecord(ev[5], s);
 }

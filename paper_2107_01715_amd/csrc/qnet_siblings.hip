@@ -716,19 +716,32 @@ __global__ void __launch_bounds__(kThreads, 2) conv_siblings_kernel(FusedConvArg
     first.ask(W2r, lane, wave, 16);
     lds_barrier();       // x1 complete; the frames are read: conv2 may write x2 over them
 
-    // ---- conv2 and conv3: 64 rows per fragment of a wavefront; two sizes of
-    // unrolled code each, the larger run again for what it leaves ----
-    const int rows2 = 81 + cn.n2, rows3 = 49 + cn.n3;
-    if (rows2 > 3 * 64) conv_group<P, 5, false>(sh, a, W2r, first, lane, wave, 0, rows2, 0);
-    if (rows2 > 5 * 64) first.ask(W2r, lane, wave, 16);
-    if (rows2 <= 3 * 64 || rows2 > 5 * 64)
-      conv_group<P, 3, false>(sh, a, W2r, first, lane, wave, rows2 > 5 * 64 ? 5 : 0, rows2, 0);
+    // ---- conv2 and conv3: 64 rows per fragment of a wavefront, unrolled code
+    // for several counts; the largest leaves what is past it to a second turn.
+    // A group of 18 has 2 to 5 fragments of conv2 and 2 to 9 of conv3 (3.7 and
+    // 4.5 on average): with code for 3 and 5, 4 and 8 only, which run 4.2 and
+    // 5.8, 256 searches of A = 18, d = 3 take 3% longer (53 KB of code: two
+    // CUs' 64 KB of instruction cache hold it) ----
+    const int rows2 = 81 + cn.n2, rows3 = 49 + cn.n3, frags2 = (rows2 + 63) >> 6, frags3 = (rows3 + 63) >> 6;
+    if (frags2 > 4) conv_group<P, 5, false>(sh, a, W2r, first, lane, wave, 0, rows2, 0);
+    if (frags2 > 5) first.ask(W2r, lane, wave, 16);
+    if (frags2 <= 4 || frags2 > 5) {
+      const int f0 = frags2 > 5 ? 5 : 0, left = frags2 - f0;
+      if (left <= 2) conv_group<P, 2, false>(sh, a, W2r, first, lane, wave, f0, rows2, 0);
+      else if (left <= 3) conv_group<P, 3, false>(sh, a, W2r, first, lane, wave, f0, rows2, 0);
+      else conv_group<P, 4, false>(sh, a, W2r, first, lane, wave, f0, rows2, 0);
+    }
     first.ask(W3r, lane, wave, 18);
     lds_barrier();
-    if (rows3 > 4 * 64) conv_group<P, 8, true>(sh, a, W3r, first, lane, wave, 0, rows3, cur.i0);
-    if (rows3 > 8 * 64) first.ask(W3r, lane, wave, 18);
-    if (rows3 <= 4 * 64 || rows3 > 8 * 64)
-      conv_group<P, 4, true>(sh, a, W3r, first, lane, wave, rows3 > 8 * 64 ? 8 : 0, rows3, cur.i0);
+    if (frags3 > 6) conv_group<P, 8, true>(sh, a, W3r, first, lane, wave, 0, rows3, cur.i0);
+    if (frags3 > 8) first.ask(W3r, lane, wave, 18);
+    if (frags3 <= 6 || frags3 > 8) {
+      const int f0 = frags3 > 8 ? 8 : 0, left = frags3 - f0;
+      if (left <= 2) conv_group<P, 2, true>(sh, a, W3r, first, lane, wave, f0, rows3, cur.i0);
+      else if (left <= 3) conv_group<P, 3, true>(sh, a, W3r, first, lane, wave, f0, rows3, cur.i0);
+      else if (left <= 4) conv_group<P, 4, true>(sh, a, W3r, first, lane, wave, f0, rows3, cur.i0);
+      else conv_group<P, 6, true>(sh, a, W3r, first, lane, wave, f0, rows3, cur.i0);
+    }
     lds_barrier();       // the background's rows are in LDS; x2 is read
 
     // ---- every child's unaffected pixels: a thread copies 16-byte chunk c of

@@ -179,7 +179,7 @@ void launch_fc1_mfma(int prec, long long n, const void* x3, const void* w, const
 // fc1 with fc2 folded into its epilogue (BF16 / FP8; w2 [32][512] in the
 // operand type, bias b2, accumulator scale scale2): fc2 takes the fc1
 // outputs rounded to the operand type, as launch_fc1_mfma stores them; an
-// fc1 workgroup of 256 x 256 sums fc2 over its 256 neurons into part [2][n][32]
+// fc1 workgroup of 256 x 256 sums fc2 over its 256 neurons into part [2][n][20]
 // FP32, then a second kernel adds the two halves in order and writes V[item] =
 // max over the item's A actions and the q0 rows of root items; the stacks of
 // smaller tiles leave fc1's outputs in part, [n][512] in the operand type, and

@@ -431,6 +431,18 @@ bool conv1_by_groups(const bcts_ctx* c, const Plan::Chunk& ch) {
   return grouped < per_stack;
 }
 
+// Descriptors of a chunk's items, from the segments that hold them.
+void enqueue_item_desc(const Plan& p, char* A, const Plan::Chunk& ch, const RootInfo* roots, const FrameBases& fb,
+                       ItemDesc* desc, hipStream_t s) {
+  auto holds = [&](long long item) {          // index of the segment that holds `item`
+    return (int)(std::upper_bound(p.segs.begin(), p.segs.end(), item,
+                                  [](long long i, const Seg& sg) { return i < sg.item0; }) - p.segs.begin()) - 1;
+  };
+  const int first = holds(ch.i0), last = holds(ch.i1 - 1);
+  launch_item_desc(ch.i0, ch.i1 - ch.i0, reinterpret_cast<const Seg*>(A + p.o_segs) + first, last - first + 1, roots, fb,
+                   desc, s);
+}
+
 // Q-network chunk ci of the plan.  With `cev` (6 events) its launches are
 // bracketed.
 bcts_status enqueue_qnet_chunk(bcts_ctx* c, const Plan& p, char* A, ItemDesc* desc, char* ws, const FrameBases& fb,
@@ -443,7 +455,7 @@ bcts_status enqueue_qnet_chunk(bcts_ctx* c, const Plan& p, char* A, ItemDesc* de
   const FusedGroup* groups = reinterpret_cast<const FusedGroup*>(A + p.o_groups);
   const Plan::Chunk& ch = p.chunks[ci];
   const long long cnt = ch.i1 - ch.i0;
-  launch_item_desc(ch.i0, cnt, reinterpret_cast<const Seg*>(A + p.o_segs), (int)p.segs.size(), roots, fb, desc, s);
+  enqueue_item_desc(p, A, ch, roots, fb, desc, s);
   if (!p.fused) {
     if (c->prec == P_FP32 && c->q.split) {
       launch_qnet_split(c->q, desc, cnt, ChunkGroups{groups + ch.g0, ch.g1 - ch.g0, ch.i0, ch.max_group}, ws, V + ch.i0, q0, s, cev);
@@ -502,7 +514,7 @@ bcts_status enqueue_tail(bcts_ctx* c, const Plan& p, char* A, ItemDesc* desc, ch
   const FusedGroup* groups = reinterpret_cast<const FusedGroup*>(A + p.o_groups);
   for (const auto& tc : p.tail_chunks) {
     const long long cnt = tc.i1 - tc.i0;
-    launch_item_desc(tc.i0, cnt, reinterpret_cast<const Seg*>(A + p.o_segs), (int)p.segs.size(), roots, fb, desc, s);
+    enqueue_item_desc(p, A, tc, roots, fb, desc, s);
     if (c->q.split) {
       launch_qnet_split(c->q, desc, cnt, ChunkGroups{groups + tc.g0, tc.g1 - tc.g0, tc.i0, tc.max_group}, ws, V + tc.i0, q0, s);
       continue;

@@ -730,16 +730,22 @@ void run_layer(const LayerArgs& a, hipStream_t s) {
 }
 
 // item descriptors: the 4 frames of each item's stack
+// (segs: those that hold the chunk's items, in order)
 __global__ void item_desc_kernel(long long item_begin, long long n_items, const Seg* __restrict__ segs,
                                  int nsegs, const RootInfo* __restrict__ roots, FrameBases fb,
                                  ItemDesc* __restrict__ out) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n_items) return;
   const long long item = item_begin + t;
-  int lo = 0, hi = nsegs - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (segs[mid].item0 <= item) lo = mid; else hi = mid - 1;
+  // the item's segment: where equal segments would put it, else by halving
+  int lo = (int)(t * nsegs / n_items);
+  if (segs[lo].item0 > item || (lo + 1 < nsegs && segs[lo + 1].item0 <= item)) {
+    lo = 0;
+    int hi = nsegs - 1;
+    while (lo < hi) {
+      int mid = (lo + hi + 1) >> 1;
+      if (segs[mid].item0 <= item) lo = mid; else hi = mid - 1;
+    }
   }
   const Seg sg = segs[lo];
   const RootInfo& ri = roots[sg.root];

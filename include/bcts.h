@@ -217,14 +217,22 @@ void bcts_graph_destroy(bcts_graph* graph);
 /* Q-network execution choices (none changes results beyond the operand
  * precision; every choice keeps each stack's sum order fixed):
  *   BCTS_TUNE_FUSED        1 = BF16/FP8 run conv1..conv3 fused per sibling
- *                          group (default), 0 = layer-by-layer kernels
+ *                          group (default), 0 = layer-by-layer kernels.
+                          FP32 has one form: conv1..conv3 in one kernel,
+                          every operand the sum of two FP16 values on the
+                          FP16 matrix instruction (its error against 64
+                          bits is below the FP32 instruction's), or, where
+                          weights leave the range that form can scale (a
+                          row or layer past 2^+-60), layer by layer on the
+                          FP32 instruction
  *   BCTS_TUNE_FUSED_ROUND  stacks per LDS round of the fused kernel: 1..4
  *                          (BF16 caps at 3: a round of 4 exceeds the LDS)
  *   BCTS_TUNE_FUSED_CHUNK  stacks per Q-network chunk on the fused path
  *   BCTS_TUNE_LAYER_CHUNK  stacks per chunk on the layer-by-layer path
  *                          (also the FP32 correction evaluations below);
  *                          default 65,536 (about 100 KB of FP32 workspace
- *                          per stack)
+ *                          per stack held, 29 KB of it used outside the
+ *                          layer-by-layer kernels)
  *   BCTS_TUNE_CORR_FP32    1 = (default) the Q-network inputs of the
  *                          correction -- Q(s_0, .), which fixes pi_o, and the
  *                          depth-1 values of the Bellman errors (Prop. 3.6)
@@ -252,8 +260,8 @@ void bcts_graph_destroy(bcts_graph* graph);
  *                          The products of each 8 consecutive K values are
  *                          summed the same way by both, so the results are
  *                          the same up to FP32 addition order.
- *   BCTS_TUNE_CONV1_GROUPS layer-by-layer path (FP32, the FP32 correction
- *                          evaluations, BCTS_TUNE_FUSED = 0): conv1 by
+ *   BCTS_TUNE_CONV1_GROUPS layer-by-layer kernels (BCTS_TUNE_FUSED = 0, and
+ *                          FP32 on the FP32 instruction): conv1 by
  *                          sibling groups -- the channels a group's stacks
  *                          share (0..2) summed once per group, each
  *                          sibling's channel 3 added to that partial sum --
@@ -270,7 +278,7 @@ void bcts_graph_destroy(bcts_graph* graph);
  *                          Sec. 4.1 runtime study; the GPU is not used.  The
  *                          device kernels' FP32 arithmetic in their order:
  *                          the same bits as the GPU search.  2 = the host
- *                          for small trees (at most 32 + 9 d nodes per
+ *                          for small trees (at most 32 + 3 d nodes per
  *                          root, where one host core beats a host-buffer
  *                          GPU search), the GPU otherwise.  0 (default) =
  *                          the GPU (with BCTS_TUNE_MLP_CROSSOVER).
@@ -457,7 +465,8 @@ bcts_status bcts_debug_qnet_siblings(bcts_ctx* ctx, int32_t n, const uint8_t* st
  *   out[3] whole search ms, out[4..8] conv1/conv2/conv3/fc1/fc2 ms summed over
  *   chunks, out[9] chunks (launches per layer), out[10..15] expansion ms of
  *   levels 1..6, out[16] Q-network items, out[17] expanded nodes, out[18] 1 if
- *   the fused conv kernel ran (its time is then in out[4]; out[5..6] are 0),
+ *   the fused conv kernel ran (its time is then in out[4]; out[5..6] are 0,
+ *   as they are in FP32's one-kernel form),
  *   out[19] ms of the FP32 correction evaluations (BCTS_TUNE_CORR_FP32;
  *   included in out[1], not in out[4..8]), out[20] chunks of the
  *   layer-by-layer path whose conv1 ran by sibling groups

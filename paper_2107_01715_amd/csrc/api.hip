@@ -502,7 +502,7 @@ bcts_status enqueue_qnet_chunk(bcts_ctx* c, const Plan& p, char* A, ItemDesc* de
   return BCTS_OK;
 }
 
-// The correction's root and depth-1 evaluations in FP32 (layer kernels).
+// The correction's root and depth-1 evaluations in FP32.
 bcts_status enqueue_tail(bcts_ctx* c, const Plan& p, char* A, ItemDesc* desc, char* ws, const FrameBases& fb,
                          hipStream_t s) {
   if (p.tail_chunks.empty()) return BCTS_OK;
@@ -2283,12 +2283,14 @@ bcts_status bcts_mlp_search(bcts_ctx* c, int32_t n_roots, const float* states, i
   for (long long i = 0; i < (long long)n_roots * 100; ++i)
     if (!std::isfinite(states[i])) return fail(c, BCTS_E_INVAL, "state value %lld is not finite", i);
   // Mode 2 takes the host for small trees: one host node (a child's model
-  // step and head) costs about 1.4 us on one core, a host-buffer search on
-  // the GPU about 45 us plus 12.5 us per level (PCIe both ways, a launch per
-  // level), so the host is the faster device below 32 + 9 d nodes per root.
+  // step and head) costs about 1.4 us on one core after 6 us, a host-buffer
+  // search on the GPU about 50 us plus 4 us per level (PCIe both ways, four
+  // levels of two actions a launch), so the host is the faster device below 32 +
+  // 3 d nodes per root: 30 nodes in 4 levels 48 us against 64, 39 in 3 levels
+  // 62.5 / 63.8, 62 in 5 levels 92 / 73.5.
   long long nodes = 0;
   for (long long k = 1, cnt = 1; k <= depth; ++k) nodes += (cnt *= c->mlp.A);
-  if (c->mlp_host == 1 || (c->mlp_host == 2 && nodes <= 32 + 9LL * depth)) {
+  if (c->mlp_host == 1 || (c->mlp_host == 2 && nodes <= 32 + 3LL * depth)) {
     // the CPU BFS: every level, the leaves, the backup and the correction on
     // the host, in the device kernels' arithmetic
     double pe = 0.0, po = 0.0;

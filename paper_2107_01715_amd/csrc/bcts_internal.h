@@ -224,8 +224,8 @@ void launch_item_desc(long long item_begin, long long n_items, const Seg* segs, 
                       const RootInfo* roots, const FrameBases& fb, ItemDesc* out,
                       hipStream_t s);
 
-// Q-network over a chunk of items (descs already built): writes V[item] and
-// q0 rows.  `ws` is a workspace of qnet_workspace_bytes(chunk, prec) bytes.
+// Q-network over a chunk of items (descs already built), layer by layer: writes
+// V[item] and q0 rows.  `ws` is a workspace of qnet_workspace_bytes(chunk, prec) bytes.
 // With `ev` (6 events) the launches are bracketed: ev[0] before conv1,
 // ev[l+1] after layer l.
 void launch_qnet(int prec, const QnetDev& q, const ItemDesc* desc, long long n_items,

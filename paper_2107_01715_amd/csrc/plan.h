@@ -61,7 +61,7 @@ struct Plan {
   // The correction's own Q-network inputs (the root and depth-1 evaluations
   // of corrected roots) can run in FP32 whatever the leaf precision: they
   // then occupy the item range [tail_item0, n_items), evaluated by the FP32
-  // layer kernels in tail_chunks (whole groups, ~tail_chunk_items items each).
+  // network in tail_chunks (whole groups, ~tail_chunk_items items each).
   // tail_item0 == n_items when every item runs at the search precision.
   long long tail_item0 = 0;
   std::vector<Chunk> tail_chunks;

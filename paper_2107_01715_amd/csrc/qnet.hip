@@ -17,7 +17,10 @@
 // W[N][K] likewise, then each wavefront runs 16x16 MFMAs over its 32-row
 // slice.  Operands: FP32 (v_mfma_f32_16x16x4_f32), BF16
 // (v_mfma_f32_16x16x32_bf16) or OCP e4m3 (v_mfma_f32_16x16x32_fp8_fp8), all
-// accumulating in FP32.  The 1/255 input scaling is applied to conv1's
+// accumulating in FP32.  BF16 and FP8 run here with the fused kernels switched
+// off, FP32 for the FP8 calibration (which reads every layer's outputs) and for
+// weights whose scales the split form of qnet_split.hip cannot hold; items'
+// descriptors are made here for all of them.  The 1/255 input scaling is applied to conv1's
 // accumulator; FP8 layers rescale by 1/(input scale * weight scale).
 #include <type_traits>
 

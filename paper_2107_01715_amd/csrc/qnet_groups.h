@@ -1,4 +1,5 @@
-// conv1 by sibling groups on the layer-by-layer Q-network path.
+// Sibling groups on the Q-network paths that take a chunk's groups whole: conv1
+// of the layer-by-layer kernels, and FP32 in split FP16.
 #pragma once
 #include "bcts_internal.h"
 

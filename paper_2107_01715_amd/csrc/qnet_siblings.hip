@@ -37,10 +37,12 @@
 //     from the background.
 //
 // Measured on 1.49 M leaves of 256 roots (A = 18, depth 3), BF16: 17.1 ms in
-// the group kernel of qnet_fused.hip, 6.0 ms here; FP8 13.8 and 4.5;
+// the group kernel of qnet_fused.hip, 5.8 ms here; FP8 13.8 and 4.4;
 // the expansion, without the leaves' frames, 2.05 and 0.17 ms.  A group of 18
-// takes 38k clocks, of which the matrix cores are busy 14k, vector
-// instructions issue for 19k and LDS is active 21k.  What it learned on the
+// takes 37k clocks, of which the matrix cores are busy 14k, vector
+// instructions issue for 19k and LDS is active 21k: conv1 7k, conv2 7k and
+// conv3 11k with the waits at their ends, the next group's lists, tables and
+// frames 5k, the copies of unaffected pixels 3k.  What it learned on the
 // way: one wavefront per SIMD with 512 registers was slower (it can issue one
 // instruction per 4 clocks, and accumulators in the upper registers are
 // moved), as was any code past the 64 KB instruction cache that two CUs

@@ -48,9 +48,9 @@ def test_bits_do_not_depend_on_the_batch():
     ctx.close()
 
 
-@pytest.mark.parametrize("scale", [1.0, 2.0 ** 9, 2.0 ** -12])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 9, 2.0 ** -12, 2.0 ** 80])
 def test_against_64_bits(scale):
-    """Layer weights of very different sizes.  Operands carry 22 bits and the
+    """Layer weights of very different sizes (2^80: on the FP32 instruction).  Operands carry 22 bits and the
     smallest product is left out (2^-22): 3 x 2^-22 of a layer's absolute sum
     at most, some 2^-20 of its result where half of the sum cancels; four
     layers and fc2: 2^-18."""

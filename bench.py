@@ -61,10 +61,12 @@ HBM_PEAK_GBS = 8000.0
 LAYER_FLOPS = {"conv1": 2 * 400 * 32 * 256, "conv2": 2 * 81 * 64 * 512, "conv3": 2 * 49 * 64 * 576,
                "fc1": 2 * 512 * 3136, "fc2": 2 * A * 512}
 LAYER_KERNEL = {"conv1": "layer_kernel<0,P>", "conv2": "layer_kernel<1,P>", "conv3": "layer_kernel<2,P>",
-                "fc1": "fc1_kernel<P>", "fc2": "layer_kernel<4,P>", "conv_fused": "conv_fused_kernel<P,T>"}
+                "fc1": "fc1_kernel<P>", "fc2": "fc2_sum_kernel", "conv_fused": "conv_fused_kernel<P,T>",
+                "conv_siblings": "conv_siblings_kernel<P>", "conv_split": "conv_split_kernel<2,2>"}
 MIXED_SEED, SERVE_SEED, MLP_SEED = 1004, 1005, 1007
-# algorithmic bytes per new node written by the expansion: frame, positions, return, reward
-EXPAND_BYTES_PER_NODE = 7056 + 16 + 4 + 1
+# algorithmic bytes per new node written by the expansion: positions, return, reward, and the frame where one is
+# rendered (the leaves' frames are formed by the sibling kernel)
+EXPAND_BYTES_PER_NODE, FRAME_BYTES = 16 + 4 + 1, 7056
 # committed autotune results (per precision and shape) and FP8 scales
 TUNING_FILE = os.path.join(ROOT, "paper_2107_01715_amd", "tuning.json")
 
@@ -113,66 +115,52 @@ def agreement(act, q, ref):
             "max_rel_err": max(errs), "mean_rel_err": float(np.mean(errs))}
 
 
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "conv_fused_bf16_256roots_A18_d3_traffic.md")
-COUNTER_PROFILE = os.path.join(ROOT, "profiles", "conv_fused_fc1_bf16_fp8_256roots_A18_d3_sq_counters.md")
+TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "search_bf16_256roots_A18_d3_traffic.md")
+COUNTER_PROFILE = os.path.join(ROOT, "profiles", "search_256roots_A18_d3_sq_counters.md")
+SIBLING_SOURCES = ("qnet_siblings.hip", "qnet_operand.h")
 
 
-def _profile_value(path, pattern):
-    """A figure from a committed counter summary, only while the fused
-    kernel's source (and the header that fixes its output layout) is the one
-    it was measured on (else None)."""
+def _profile_value(path, pattern, sources):
+    """A figure from a committed counter summary, only while the sources it
+    was measured on are the tree's (else None)."""
     import hashlib
     import re
     csrc = os.path.join(ROOT, "paper_2107_01715_amd", "csrc")
     try:
         text = open(path).read()
-        src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("qnet_fused.hip", "bcts_internal.h"))
+        src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in sources)
     except OSError:
         return None
     m = re.search(pattern, text)
-    h = re.search(r"source_sha256 qnet_fused.hip\+bcts_internal.h:\s*([0-9a-f]{64})", text)
+    h = re.search(r"source_sha256 %s:\s*([0-9a-f]{64})" % re.escape("+".join(sources)), text)
     if not m or not h or h.group(1) != hashlib.sha256(src).hexdigest():
         return None
     return float(m.group(1))
-
-
-EXPAND_PROFILE = os.path.join(ROOT, "profiles", "expand_256roots_A18_d3_traffic.md")
 
 
 def measured_expand_traffic():
-    """HBM bytes per new node of the expansion (FETCH_SIZE + WRITE_SIZE,
+    """HBM bytes per rendered node of the expansion (FETCH_SIZE + WRITE_SIZE,
     copy-calibrated) while its kernel's source is the one measured."""
-    import hashlib
-    import re
-    try:
-        text = open(EXPAND_PROFILE).read()
-        src = open(os.path.join(ROOT, "paper_2107_01715_amd", "csrc", "expand.hip"), "rb").read()
-    except OSError:
-        return None
-    m = re.search(r"traffic_bytes_per_node:\s*([0-9.]+)", text)
-    h = re.search(r"source_sha256 expand.hip:\s*([0-9a-f]{64})", text)
-    if not m or not h or h.group(1) != hashlib.sha256(src).hexdigest():
-        return None
-    return float(m.group(1))
+    return _profile_value(TRAFFIC_PROFILE, r"traffic_bytes_per_rendered_node:\s*([0-9.]+)", ("expand.hip",))
 
 
-def measured_traffic(kernel, precision, fused, tuned):
+def measured_traffic(kernel, precision):
     """HBM bytes per stack of the dominant kernel (FETCH_SIZE + WRITE_SIZE,
-    copy-calibrated), for the kernel and round size it was measured on.  The
-    per-stack figure does not depend on how the stacks are chunked."""
-    if kernel != "conv_fused" or precision != "bf16" or not fused or tuned.get("round") != 3:
+    copy-calibrated).  The per-stack figure does not depend on how the stacks
+    are chunked."""
+    if kernel != "conv_siblings" or precision != "bf16":
         return None
-    return _profile_value(TRAFFIC_PROFILE, r"traffic_bytes_per_stack:\s*([0-9.]+)")
+    return _profile_value(TRAFFIC_PROFILE, r"traffic_bytes_per_stack:\s*([0-9.]+)", SIBLING_SOURCES)
 
 
-def measured_executed_flops(kernel, precision, fused, tuned):
-    """Matrix-core FLOP per stack the fused kernel executes (counter
-    SQ_INSTS_VALU_MFMA_MOPS_* x 512), for the launch shape it was measured on."""
-    if kernel != "conv_fused" or precision not in ("bf16", "fp8") or not fused or tuned.get("round") != 3:
-        return None
-    if precision == "fp8" and not tuned.get("fp8_k128"):
-        return None
-    return _profile_value(COUNTER_PROFILE, r"executed_flop_per_stack %s:\s*([0-9.]+)" % precision)
+def measured_executed_flops(kernel, precision):
+    """Matrix-core FLOP per stack the dominant kernel executes (counter
+    SQ_INSTS_VALU_MFMA_MOPS_* x 512), at the headline shape."""
+    if kernel == "conv_siblings":
+        return _profile_value(COUNTER_PROFILE, r"executed_flop_per_stack %s:\s*([0-9.]+)" % precision, SIBLING_SOURCES)
+    if kernel == "conv_split":
+        return _profile_value(COUNTER_PROFILE, r"executed_flop_per_stack fp32:\s*([0-9.]+)", ("qnet_split.hip",))
+    return None
 
 
 def _setup(seed, n_roots, budget=0):
@@ -769,9 +757,12 @@ def main():
     n_items = kern[16]
     fused = kern[18] > 0.5
     main_items = n_items - N_ROOTS * (A + 1) if fused and kern[19] > 0 else n_items
-    names = ("conv_fused", None, None, "fc1", "fc2") if fused else ("conv1", "conv2", "conv3", "fc1", "fc2")
+    siblings = fused and (args.precision == "bf16" or bool(tuned.get("fp8_k128", 1)))
+    conv = "conv_siblings" if siblings else "conv_fused" if fused else "conv_split"
+    one_kernel = fused or kern[5] < 0.01 * kern[4]
+    names = (conv, None, None, "fc1", "fc2") if one_kernel else ("conv1", "conv2", "conv3", "fc1", "fc2")
     flops_of = dict(LAYER_FLOPS)
-    flops_of["conv_fused"] = LAYER_FLOPS["conv1"] + LAYER_FLOPS["conv2"] + LAYER_FLOPS["conv3"]
+    flops_of[conv] = LAYER_FLOPS["conv1"] + LAYER_FLOPS["conv2"] + LAYER_FLOPS["conv3"]
     kernels = {}
     for i, name in enumerate(names):
         if name is None:
@@ -798,23 +789,30 @@ def main():
     peak = PEAK_TFLOPS[args.precision]
     exp_nodes = kern[17]
     exp_ms = kern[0]
-    exp_gbs = exp_nodes * EXPAND_BYTES_PER_NODE / (exp_ms * 1e-3) / 1e9 if exp_ms > 0 else None
+    exp_frames = exp_nodes - (leaves if siblings else 0)
+    exp_gbs = ((exp_nodes * EXPAND_BYTES_PER_NODE + exp_frames * FRAME_BYTES) / (exp_ms * 1e-3) / 1e9
+               if exp_ms > 0 else None)
     qnet_tflops = leaves * sum(LAYER_FLOPS.values()) / (kern[1] * 1e-3) / 1e12 if kern[1] > 0 else None
-    per_stack = measured_traffic(dom, args.precision, fused, tuned)
+    per_stack = measured_traffic(dom, args.precision)
     traffic = per_stack * main_items / max(kern[9], 1) if per_stack is not None else None
-    ex_stack = measured_executed_flops(dom, args.precision, fused, tuned)
+    ex_stack = measured_executed_flops(dom, args.precision)
     ex_tflops = (ex_stack * main_items / (kernels[dom]["ms_per_step"] * 1e-3) / 1e12
                  if ex_stack is not None and kernels[dom]["ms_per_step"] > 0 else None)
+    # FP32 executes FP16 products (two or three for one)
+    ex_peak = PEAK_TFLOPS["bf16"] if dom == "conv_split" else peak
     roofline = {"bound": "mfma", "kernel": LAYER_KERNEL[dom].replace("P", args.precision).replace("T", str(tuned.get("round", ""))),
-                "layer": dom, "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
-                "flop_per_launch": flops_of[dom] * main_items / max(kern[9], 1),
+                "layer": dom, "achieved": ex_tflops if ex_tflops is not None else ach,
+                "peak": ex_peak if ex_tflops is not None else peak, "unit": "TFLOP/s",
+                "frac": ex_tflops / ex_peak if ex_tflops is not None else ach / peak,
+                "flop_per_launch": (ex_stack or flops_of[dom]) * main_items / max(kern[9], 1),
                 "avg_launch_ms": kernels[dom]["avg_launch_ms"], "traffic": traffic,
                 "traffic_unit": "bytes per launch (HBM, rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-                "achieved_is": "algorithmic FLOP (the three plain convolutions per stack) / HIP-event kernel time",
-                "executed": ({"achieved": ex_tflops, "frac": ex_tflops / peak, "flop_per_stack": ex_stack,
-                              "what": "matrix-core FLOP the kernel executes (rocprofv3 SQ_INSTS_VALU_MFMA_MOPS x 512: "
-                                      "conv1 shared by siblings, padded rows) / the same kernel time"}
-                             if ex_tflops is not None else None)}
+                "achieved_is": ("matrix-core FLOP the kernel executes (rocprofv3 SQ_INSTS_VALU_MFMA_MOPS x 512) / "
+                                "HIP-event kernel time" if ex_tflops is not None else
+                                "algorithmic FLOP (the three plain convolutions per stack) / HIP-event kernel time"),
+                "algorithmic": {"achieved": ach, "flop_per_stack": flops_of[dom],
+                                "what": "the three plain convolutions of every stack / the same kernel time; siblings "
+                                        "share most of that work, so this can exceed the peak"}}
 
     lat = np.array(per_step) if per_step else np.array([ms_step])
     out = {
@@ -843,10 +841,10 @@ def main():
         "qnet_stage_tflops": qnet_tflops,
         "expand": {"bound": "hbm", "achieved": exp_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                    "frac": exp_gbs / HBM_PEAK_GBS if exp_gbs else None, "nodes": exp_nodes,
-                   "bytes_per_node": EXPAND_BYTES_PER_NODE,
-                   "traffic_bytes_per_node": measured_expand_traffic(),
-                   "achieved_is": "algorithmic bytes per node x new nodes / HIP-event time of the three launches; "
-                                  "traffic_bytes_per_node from rocprofv3 FETCH_SIZE + WRITE_SIZE"},
+                   "frames": exp_frames, "bytes_per_node": EXPAND_BYTES_PER_NODE, "bytes_per_frame": FRAME_BYTES,
+                   "traffic_bytes_per_rendered_node": measured_expand_traffic(),
+                   "achieved_is": "algorithmic bytes (every node's row, the rendered frames) / HIP-event time of the "
+                                  "three launches; traffic from rocprofv3 FETCH_SIZE + WRITE_SIZE"},
         "roofline": roofline,
         "cpu_baseline": cpu,
     }

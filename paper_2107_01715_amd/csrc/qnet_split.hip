@@ -7,11 +7,15 @@
 // w_lo x_lo (2^-24 of w x and less, of either sign).  The pixels of conv1 are
 // whole numbers, exact in FP16: two products there.  A sum over K = 32 is one
 // v_mfma_f32_16x16x32_f16 and one rounding where v_mfma_f32_16x16x4_f32 makes
-// 32, so the sums' error falls by more than the operands' rises: against 64
-// bits 2.0e-7 of the largest Q over 256 searches of A = 6, d = 3 (2.8e-7 on the
-// FP32 instruction), 1.1e-6 for one search (1.7e-6).
+// 32.  It rounds within, too, every 4 to 8 values, so long sums are cut: the
+// small products have sums of their own, and K runs in slices summed from zero
+// (conv2 4 steps a slice, conv3 3, fc1 14).  The sums' error then falls by more
+// than the operands' rises.  Against 64 bits, of a root's largest |Q| over 768
+// searches of A = 6, d = 3: 3.0e-7 on average and 1.6e-6 at most, where the FP32
+// instruction has 6.8e-7 and 3.5e-6 (4.5e-7 and 2.4e-6 with one sum for all
+// products and no slices in the conv layers, 3% faster).
 //
-// Time, 256 searches of A = 6, d = 3 (57,088 stacks): conv layers 2.23 ms where
+// Time, 256 searches of A = 6, d = 3 (57,088 stacks): conv layers 2.3 ms where
 // layer-by-layer kernels on v_mfma_f32_16x16x4_f32 took 5.86 (the FP32
 // instruction alone 4.2 at the card's 154 TFLOP/s), fc1 0.56 (1.65).
 //
@@ -77,27 +81,40 @@ __device__ __forceinline__ h16x8 ldw(const void* w, int blk, unsigned off) {
   return *reinterpret_cast<const h16x8*>(reinterpret_cast<const char*>(w) + blk * 1024 + off);
 }
 
-// One K step of a wavefront's tiles: the small products first
+// One K step of a wavefront's tiles: w_lo x_hi and w_hi x_lo in sums of their own
 template <int T, int NF>
-__device__ __forceinline__ void step(f32x4 (&acc)[T][NF], const h16x8 (&w)[NF][2], const h16x8 (&x)[T][2]) {
+__device__ __forceinline__ void step(f32x4 (&acc)[T][NF], f32x4 (&low)[T][NF], const h16x8 (&w)[NF][2],
+                                     const h16x8 (&x)[T][2]) {
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
-    for (int f = 0; f < NF; ++f) acc[t][f] = mma(w[f][1], x[t][0], acc[t][f]);
+    for (int f = 0; f < NF; ++f) low[t][f] = mma(w[f][1], x[t][0], low[t][f]);
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
-    for (int f = 0; f < NF; ++f) acc[t][f] = mma(w[f][0], x[t][1], acc[t][f]);
+    for (int f = 0; f < NF; ++f) low[t][f] = mma(w[f][0], x[t][1], low[t][f]);
 #pragma unroll
   for (int t = 0; t < T; ++t)
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[t][f] = mma(w[f][0], x[t][0], acc[t][f]);
 }
 
+// The end of a slice of K: its sums join the total, the next slice starts from zero
+template <int T, int NF>
+__device__ __forceinline__ void take(f32x4 (&tot)[T][NF], f32x4 (&acc)[T][NF], bool first) {
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      tot[t][f] = first ? acc[t][f] : tot[t][f] + acc[t][f];
+      acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
 // ReLU(acc scale + bias) of a wavefront's row tiles, split: st(row, channel / 8,
 // byte offset in the chunk, hi, lo) for each 8 (NF 2) or 4 (NF 1) channels
 template <int NF, int M, int RG, int T, class St>
-__device__ __forceinline__ void store_rows(const f32x4 (&acc)[T][NF], const float* __restrict__ scale,
+__device__ __forceinline__ void store_rows(const f32x4 (&acc)[T][NF], const f32x4 (&low)[T][NF], const float* __restrict__ scale,
                                            const float* __restrict__ bias, int ng, int rg, int r16, int g, St st) {
   // fragment f holds channels 32 (f / 2) + 8 g + 4 (f & 1) + 0..3
   constexpr int C = 4 * NF;
@@ -117,7 +134,7 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[T][NF], const floa
       float v[2];
 #pragma unroll
       for (int k = 0; k < 2; ++k)
-        v[k] = fmaxf(fmaf(acc[t][(e + k) >> 2][(e + k) & 3], sc[e + k], b[e + k]), 0.f);
+        v[k] = fmaxf(fmaf(acc[t][(e + k) >> 2][(e + k) & 3] + low[t][(e + k) >> 2][(e + k) & 3], sc[e + k], b[e + k]), 0.f);
       unsigned h, l;
       split2(v[0], v[1], h, l);
       hi[e / 2] = h;
@@ -130,6 +147,8 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[T][NF], const floa
 template <int NI, int NF>
 __global__ void __launch_bounds__(512) conv_split_kernel(SplitConvArgs a) {
   constexpr int NG = 4 / NF, RG = 8 / NG;
+  // K steps of weights and pixels held: what fits the registers (256 a lane)
+  constexpr int WD = NI == 1 ? 3 : 2, XD = NI == 1 ? 2 : 1;
   constexpr int M2 = NI * 81, T2 = ((M2 + 15) / 16 + RG - 1) / RG;       // row tiles per wavefront
   constexpr int M3 = NI * 49, T3 = ((M3 + 15) / 16 + RG - 1) / RG;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[NI * (kX1 + kX2)];
@@ -284,41 +303,42 @@ __global__ void __launch_bounds__(512) conv_split_kernel(SplitConvArgs a) {
           p0[t] = q / 9 * 40 + q % 9;
           base[t] = i * kX1;
         }
-        f32x4 acc[T2][NF];
+        f32x4 acc[T2][NF], low[T2][NF], tot[T2][NF];
 #pragma unroll
         for (int t = 0; t < T2; ++t)
 #pragma unroll
-          for (int f = 0; f < NF; ++f) acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int f = 0; f < NF; ++f) acc[t][f] = low[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
         unsigned wo = (ng * NF * 128 + lane) * 16 - 8192;
-        h16x8 w[3][NF][2];
+        h16x8 w[WD][NF][2];
         auto load_w = [&](int ks) {
           wo = (unsigned)fresh((int)wo + 8192);
 #pragma unroll
           for (int f = 0; f < NF; ++f)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) w[ks % 3][f][pl] = ldw(a.w[1], f * 2 + pl, wo);
+            for (int pl = 0; pl < 2; ++pl) w[ks % WD][f][pl] = ldw(a.w[1], f * 2 + pl, wo);
         };
-        h16x8 x[2][T2][2];
+        h16x8 x[XD][T2][2];
         auto load_x = [&](int ks) {
           const int kh = ks >> 2, kw = ks & 3, d = kh * 20 + (kw >> 1) + 10 * (kw & 1);
 #pragma unroll
           for (int t = 0; t < T2; ++t) {
             const int p = p0[t] + d, o = base[t] + p * 128 + ((g ^ (p & 7)) << 4);
-            x[ks & 1][t][0] = *reinterpret_cast<const h16x8*>(x1 + o);
-            x[ks & 1][t][1] = *reinterpret_cast<const h16x8*>(x1 + (o ^ 64));
+            x[ks % XD][t][0] = *reinterpret_cast<const h16x8*>(x1 + o);
+            x[ks % XD][t][1] = *reinterpret_cast<const h16x8*>(x1 + (o ^ 64));
           }
         };
-        load_w(0);
-        load_w(1);
-        load_x(0);
+#pragma unroll
+        for (int ks = 0; ks < WD - 1; ++ks) load_w(ks);
+        if (XD > 1) load_x(0);
 #pragma unroll
         for (int ks = 0; ks < 16; ++ks) {
-          if (ks + 2 < 16) load_w(ks + 2);
-          if (ks + 1 < 16) load_x(ks + 1);
-          step<T2, NF>(acc, w[ks % 3], x[ks & 1]);
+          if (ks + WD - 1 < 16) load_w(ks + WD - 1);
+          if (ks + XD - 1 < 16) load_x(ks + XD - 1);
+          step<T2, NF>(acc, low, w[ks % WD], x[ks % XD]);
+          if (ks % 4 == 3) take<T2, NF>(tot, acc, ks < 4);
           __builtin_amdgcn_sched_barrier(0);
         }
-        store_rows<NF, M2, RG, T2>(acc, a.scale[1], a.bias[1], ng, rg, r16, g, [&](int m, int c8, int half, auto hi, auto lo) {
+        store_rows<NF, M2, RG, T2>(tot, low, a.scale[1], a.bias[1], ng, rg, r16, g, [&](int m, int c8, int half, auto hi, auto lo) {
           const int i = m / 81, q = m - i * 81;
           unsigned char* o = x2 + i * kX2 + q * 256 + ((c8 ^ (q & 7)) << 4) + half;
           *reinterpret_cast<decltype(hi)*>(o) = hi;
@@ -339,41 +359,42 @@ __global__ void __launch_bounds__(512) conv_split_kernel(SplitConvArgs a) {
           p0[t] = q / 7 * 9 + q % 7;
           base[t] = i * kX2;
         }
-        f32x4 acc[T3][NF];
+        f32x4 acc[T3][NF], low[T3][NF], tot[T3][NF];
 #pragma unroll
         for (int t = 0; t < T3; ++t)
 #pragma unroll
-          for (int f = 0; f < NF; ++f) acc[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int f = 0; f < NF; ++f) acc[t][f] = low[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
         unsigned wo = (ng * NF * 128 + lane) * 16 - 8192;
-        h16x8 w[3][NF][2];
+        h16x8 w[WD][NF][2];
         auto load_w = [&](int ks) {
           wo = (unsigned)fresh((int)wo + 8192);
 #pragma unroll
           for (int f = 0; f < NF; ++f)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) w[ks % 3][f][pl] = ldw(a.w[2], f * 2 + pl, wo);
+            for (int pl = 0; pl < 2; ++pl) w[ks % WD][f][pl] = ldw(a.w[2], f * 2 + pl, wo);
         };
-        h16x8 x[2][T3][2];
+        h16x8 x[XD][T3][2];
         auto load_x = [&](int ks) {
           const int tap = ks >> 1, d = tap / 3 * 9 + tap % 3;
 #pragma unroll
           for (int t = 0; t < T3; ++t) {
             const int p = p0[t] + d, o = base[t] + p * 256 + (((4 * (ks & 1) + g) ^ (p & 7)) << 4);
-            x[ks & 1][t][0] = *reinterpret_cast<const h16x8*>(x2 + o);
-            x[ks & 1][t][1] = *reinterpret_cast<const h16x8*>(x2 + o + 128);
+            x[ks % XD][t][0] = *reinterpret_cast<const h16x8*>(x2 + o);
+            x[ks % XD][t][1] = *reinterpret_cast<const h16x8*>(x2 + o + 128);
           }
         };
-        load_w(0);
-        load_w(1);
-        load_x(0);
+#pragma unroll
+        for (int ks = 0; ks < WD - 1; ++ks) load_w(ks);
+        if (XD > 1) load_x(0);
 #pragma unroll
         for (int ks = 0; ks < 18; ++ks) {
-          if (ks + 2 < 18) load_w(ks + 2);
-          if (ks + 1 < 18) load_x(ks + 1);
-          step<T3, NF>(acc, w[ks % 3], x[ks & 1]);
+          if (ks + WD - 1 < 18) load_w(ks + WD - 1);
+          if (ks + XD - 1 < 18) load_x(ks + XD - 1);
+          step<T3, NF>(acc, low, w[ks % WD], x[ks % XD]);
+          if (ks % 3 == 2) take<T3, NF>(tot, acc, ks < 3);
           __builtin_amdgcn_sched_barrier(0);
         }
-        store_rows<NF, M3, RG, T3>(acc, a.scale[2], a.bias[2], ng, rg, r16, g, [&](int m, int c8, int half, auto hi, auto lo) {
+        store_rows<NF, M3, RG, T3>(tot, low, a.scale[2], a.bias[2], ng, rg, r16, g, [&](int m, int c8, int half, auto hi, auto lo) {
           const int i = m / 49, q = m - i * 49;
           if (s + i >= end) return;
           unsigned char* o = a.x3 + (item + s + i) * kSplitRow + (q * 2 + (c8 >> 2)) * 128 + (c8 & 3) * 16 + half;
@@ -425,11 +446,11 @@ fc1_split_kernel(long long n, const unsigned char* __restrict__ X, const unsigne
 #pragma unroll
     for (int j = 0; j < PER; ++j) load_lds16(src[j] + st * 128, base + j * T * 16);
   };
-  f32x4 acc[FN][FM], tot[FN][FM];
+  f32x4 acc[FN][FM], low[FN][FM], tot[FN][FM];
 #pragma unroll
   for (int i = 0; i < FN; ++i)
 #pragma unroll
-    for (int j = 0; j < FM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < FM; ++j) acc[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   issue(st0);
   issue(st0 + 1);
   for (int z = st0; z < st1; z += SS) {
@@ -452,9 +473,9 @@ fc1_split_kernel(long long n, const unsigned char* __restrict__ X, const unsigne
       for (int i = 0; i < FN; ++i) {
         const h16x8 wh = ld(Ws, (wn * FN + i) * 16 + r16, g), wl = ld(Ws, (wn * FN + i) * 16 + r16, 4 + g);
 #pragma unroll
-        for (int j = 0; j < FM; ++j) acc[i][j] = mma(wl, x[j][0], acc[i][j]);
+        for (int j = 0; j < FM; ++j) low[i][j] = mma(wl, x[j][0], low[i][j]);
 #pragma unroll
-        for (int j = 0; j < FM; ++j) acc[i][j] = mma(wh, x[j][1], acc[i][j]);
+        for (int j = 0; j < FM; ++j) low[i][j] = mma(wh, x[j][1], low[i][j]);
 #pragma unroll
         for (int j = 0; j < FM; ++j) acc[i][j] = mma(wh, x[j][0], acc[i][j]);
       }
@@ -463,8 +484,9 @@ fc1_split_kernel(long long n, const unsigned char* __restrict__ X, const unsigne
     for (int i = 0; i < FN; ++i)
 #pragma unroll
       for (int j = 0; j < FM; ++j) {
+        acc[i][j] += low[i][j];
         tot[i][j] = z == st0 ? acc[i][j] : tot[i][j] + acc[i][j];
-        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        acc[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
   }
 #pragma unroll
@@ -497,8 +519,9 @@ fc1_split_kernel(long long n, const unsigned char* __restrict__ X, const unsigne
 // ---- fc2 ----------------------------------------------------------------
 // Q = h W2^T + b in FP32 (v_mfma_f32_16x16x4_f32), V = max over the stack's A
 // actions, the q0 rows of root items.  IPB stacks a workgroup, an eighth of K a
-// wavefront, the eight sums added in pairs.  SLICES: H holds fc1's slices, of which h
-// is formed as fc1_split_kernel forms it; 14 KB a stack, so few stacks a workgroup.
+// wavefront, the eight sums added in pairs.  SLICES: H holds fc1's slices, of
+// which h is formed as fc1_split_kernel forms it; 14 KB a stack, so few stacks a
+// workgroup.
 template <bool SLICES, int IPB>
 __global__ void __launch_bounds__(512) fc2_split_kernel(long long n, const float* __restrict__ H,
                                                         const float* __restrict__ scale1, const float* __restrict__ bias1,
@@ -670,11 +693,11 @@ void launch_qnet_split(const QnetDev& q, const ItemDesc* desc, long long n, cons
   }
   if (ev) (void)hipEventRecord(ev[4], s);
   if (slices)
-    hipLaunchKernelGGL((fc2_split_kernel<true, 4>), dim3((unsigned)((n + 3) / 4)), dim3(512), 0, s, n, part, q.ssplit[3], q.bsplit[3], q.w[4], q.b[4],
-                       desc, V, q0);
+    hipLaunchKernelGGL((fc2_split_kernel<true, 4>), dim3((unsigned)((n + 3) / 4)), dim3(512), 0, s, n, part,
+                       q.ssplit[3], q.bsplit[3], q.w[4], q.b[4], desc, V, q0);
   else
-    hipLaunchKernelGGL((fc2_split_kernel<false, 16>), dim3((unsigned)((n + 15) / 16)), dim3(512), 0, s, n, h, q.ssplit[3], q.bsplit[3], q.w[4], q.b[4],
-                       desc, V, q0);
+    hipLaunchKernelGGL((fc2_split_kernel<false, 16>), dim3((unsigned)((n + 15) / 16)), dim3(512), 0, s, n, h,
+                       q.ssplit[3], q.bsplit[3], q.w[4], q.b[4], desc, V, q0);
   if (ev) (void)hipEventRecord(ev[5], s);
 }
 

@@ -1233,7 +1233,10 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
     off[l][5] = o; o += (l == 1 || l == 2) ? align_up(n) : l == 3 ? align_up(fc1_tiles * fc1_tile_bytes(1)) : 0;
     off[l][6] = o; o += (l == 1 || l == 2) ? align_up(n) : 0;        // FP8 for the K = 128 instruction
   }
-  // the split planes: scales of rows and layers, then per layer planes, row scales, output scales, biases
+  // the split planes (7 MB) stay out of what the budget counts: a search that
+  // fitted a budget without them still does
+  const size_t counted = o;
+  // scales of rows and layers, then per layer planes, row scales, output scales, biases
   SplitScales sp;
   c->q.split = split_scales(W, B, &sp);
   size_t soff[4][4];
@@ -1247,7 +1250,7 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
     c->wmem = nullptr;
   }
   HIPCHECK(c, hipMalloc(&c->wmem, o));
-  c->wbytes = o;
+  c->wbytes = counted;
   char* base = static_cast<char*>(c->wmem);
   for (int l = 0; l < 5; ++l) {
     HIPCHECK(c, hipMemcpy(base + off[l][0], W[l].data(), W[l].size() * 4, hipMemcpyHostToDevice));

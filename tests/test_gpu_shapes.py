@@ -61,3 +61,31 @@ def test_host_inputs_staged_and_direct():
         act1, q1 = ctx.search_batch(pos[:n], stacks[:n], d[:n], A[:n], 0.99, corr)
         assert np.array_equal(act1, act[:n]) and np.array_equal(q1, q[:n])
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["FP32", "BF16"])
+@pytest.mark.parametrize("beam,A,d", [(1, 18, 4), (4, 9, 5), (4, 18, 3)])
+def test_kept_nodes_rendered_alone(prec, beam, A, d):
+    """A level whose every root is cut renders its kept nodes after the cut;
+    beside a root that is not cut there, all nodes before it."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_01715_amd import bcts as lib
+    ctx = lib.Context(0)
+    e = W.env_params(7)
+    ctx.set_env(e.delta, e.vel)
+    ctx.set_qnet(W.qnet_blob(W.qnet_weights(7)))
+    ctx.set_precision(getattr(lib, prec))
+    ctx.set_beam(beam)
+    corr = lib.correction(True)
+    pos, stacks = W.roots(33, 4)
+    As, ds = np.full(4, A, np.int32), np.full(4, d, np.int32)
+    act, q = ctx.search_batch(pos, stacks, ds, As, 0.99, corr)
+    As[3], ds[3] = 1 if beam == 1 else 2, d                 # blocks of at most `beam` nodes at levels 2 and 3: uncut
+    if beam == 1:
+        corr = lib.correction(False)
+        act, q = ctx.search_batch(pos[:3], stacks[:3], ds[:3], As[:3], 0.99, corr)
+    act2, q2 = ctx.search_batch(pos, stacks, ds, As, 0.99, corr)
+    assert np.array_equal(act2[:3], act[:3]) and np.array_equal(q2[:3, :A], q[:3, :A])
+    ctx.close()

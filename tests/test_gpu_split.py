@@ -39,7 +39,7 @@ def test_bits_do_not_depend_on_the_batch():
     base[:, :3] = np.repeat(base[::18, :3], 18, axis=0)     # siblings: 9 groups of 18 share channels 0..2
     stacks = np.tile(base, (102, 1, 1, 1))                  # 16,524 stacks
     whole = ctx.debug_qnet(stacks, 18)
-    for n in (1, 2, 31, 33, 161, 1023, 1025, 16384, 16385):
+    for n in (1, 2, 31, 33, 161, 768, 769, 1023, 1025, 13000, 16384, 16385):
         q = ctx.debug_qnet(stacks[:n], 18)
         assert np.array_equal(q, whole[:n]), (n, np.abs(q - whole[:n]).max())
     for n, group in ((18, 18), (162, 18), (162, 3), (1026, 18), (1026, 2), (1026, 9), (16524, 18), (16524, 6)):

@@ -150,6 +150,10 @@ bcts_status check_usable(bcts_ctx* c) {
   return BCTS_OK;
 }
 
+// Staging memory that kernels write results to: coherent, so that the host
+// sees them once an event after the kernel has completed.
+constexpr unsigned kPinnedFlags = hipHostMallocMapped | hipHostMallocCoherent;
+
 bcts_status ensure_pinned(bcts_ctx* c, size_t bytes) {
   if (c->pinned_bytes >= bytes) return BCTS_OK;
   HIPCHECK(c, hipStreamSynchronize(c->stream));
@@ -157,7 +161,7 @@ bcts_status ensure_pinned(bcts_ctx* c, size_t bytes) {
   c->pinned = nullptr;
   c->pinned_bytes = 0;
   size_t nb = std::max(bytes, (size_t)1 << 20);
-  HIPCHECK(c, hipHostMalloc((void**)&c->pinned, nb, hipHostMallocDefault));
+  HIPCHECK(c, hipHostMalloc((void**)&c->pinned, nb, kPinnedFlags));
   c->pinned_bytes = nb;
   return BCTS_OK;
 }
@@ -848,7 +852,7 @@ struct ServeEngine {
       dev = nullptr;
       return fail(c, BCTS_E_NOMEM, "hipMalloc(%zu) for the serving pool failed: %s", dev_bytes, hipGetErrorString(e));
     }
-    HIPCHECK(c, hipHostMalloc((void**)&pinned, kPinnedBytes, hipHostMallocDefault));
+    HIPCHECK(c, hipHostMalloc((void**)&pinned, kPinnedBytes, kPinnedFlags));
     pool.reset(dev_bytes - shared_bytes);
     pin_pool.reset(kPinnedBytes);
     ready = true;

@@ -410,9 +410,11 @@ bool split_scales(const std::vector<float>* W, const std::vector<float>* B, Spli
       ok = ok && std::abs(e_row[o]) <= 60;
       const int er = std::max(-60, std::min(60, e_row[o])), eo = std::max(-60, std::min(60, e_out));
       sp->row[l].push_back((float)std::ldexp(1.0, er));
-      // conv1: 1/255 as the FP32 path multiplies it
-      sp->out[l].push_back((float)std::ldexp(l == 0 ? (double)(1.f / 255.f) : 1.0, eo - er - e_in));
-      sp->bias[l].push_back((float)std::ldexp((double)B[l][o], eo));
+      // conv1: 1/255 as the FP32 path multiplies it; a conv layer's outputs are
+      // split from 2^11 times what the planes hold
+      const double held = l < 3 ? (double)kSplitLow : 1.0;
+      sp->out[l].push_back((float)std::ldexp(held * (l == 0 ? (double)(1.f / 255.f) : 1.0), eo - er - e_in));
+      sp->bias[l].push_back((float)std::ldexp(held * (double)B[l][o], eo));
     }
     bound = top;
     e_in = std::max(-60, std::min(60, e_out));
@@ -1289,7 +1291,7 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
     const std::vector<float>* v[3] = {&sp.row[l], &sp.out[l], &sp.bias[l]};
     for (int k = 0; k < 3; ++k)
       HIPCHECK(c, hipMemcpy(base + soff[l][k + 1], v[k]->data(), v[k]->size() * 4, hipMemcpyHostToDevice));
-    launch_split_weights(c->q.w[l], reinterpret_cast<const float*>(base + soff[l][1]), NK[l][0], NK[l][1], l == 3,
+    launch_split_weights(l, c->q.w[l], reinterpret_cast<const float*>(base + soff[l][1]), NK[l][0], NK[l][1],
                          base + soff[l][0], c->stream);
     c->q.wsplit[l] = base + soff[l][0];
     c->q.ssplit[l] = reinterpret_cast<const float*>(base + soff[l][2]);

@@ -164,7 +164,8 @@ struct SplitConvArgs {
   const float *scale[3], *bias[3];
   unsigned char* x3;           // [stacks][98][2][32] FP16
 };
-void launch_split_weights(const float* w, const float* row_scale, int N, int K, bool rows, void* out, hipStream_t s);
+constexpr float kSplitLow = 2048.f;                     // a low plane's factor, and the held outputs'
+void launch_split_weights(int layer, const float* w, const float* row_scale, int N, int K, void* out, hipStream_t s);
 
 // Copies fc1's W[N][K] (N a multiple of 256, eb bytes per element) into
 // stage-major tiles.

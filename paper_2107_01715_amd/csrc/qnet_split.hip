@@ -1,9 +1,9 @@
 // The FP32 Q-network on the FP16 matrix cores: every operand as the sum of two
 // FP16 values.
 //
-// An FP32 value v scaled into FP16's range is hi + lo, hi = fp16(v), lo =
-// fp16(v - hi): 22 to 23 bits of the 24, and a product w x is w_hi x_hi +
-// w_hi x_lo + w_lo x_hi, each exact in FP32, summed in FP32.  Left out is
+// An FP32 value v scaled into FP16's range is hi + lo / 2^11, hi = fp16(v), lo =
+// fp16((v - hi) 2^11): 22 to 23 bits of the 24, and a product w x is w_hi x_hi +
+// (w_hi x_lo + w_lo x_hi) / 2^11, each exact in FP32, summed in FP32.  Left out is
 // w_lo x_lo (2^-24 of w x and less, of either sign).  The pixels of conv1 are
 // whole numbers, exact in FP16: two products there.  A sum over K = 32 is one
 // v_mfma_f32_16x16x32_f16 and one rounding where v_mfma_f32_16x16x4_f32 makes
@@ -21,8 +21,11 @@
 //
 // Scaling is by powers of two, exact: a row of weights by the one that brings
 // its largest into [2^13, 2^14); a layer's outputs by the one that brings the
-// bound max_o(sum |w_o| bound_in + |b_o|) to at most 2^15.  FP16 ends at
-// 2^-24, so a value up to 2^-16 of the bound keeps its bits.
+// bound max_o(sum |w_o| bound_in + |b_o|) to at most 2^15.  FP16's normal values
+// end at 2^-14 and the low plane is held 2^11 times as large, so a value keeps
+// its 22 bits down to 2^-29 of the bound (2^-17 with the low plane as it is,
+// which the median positive output of conv3 passes: the bound grows with each
+// layer).  conv1's planes share one sum, its low one is held as it is.
 #include "bcts_internal.h"
 #include "qnet_groups.h"
 
@@ -44,12 +47,15 @@ __device__ __forceinline__ f32x4 mma(h16x8 a, h16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-// a, b as two FP16 pairs: hi, and what hi leaves of them (exact in FP32, one
-// instruction a value with its rounding to FP16)
+// a, b, held times 2^11, as two FP16 pairs: hi = fp16(a / 2^11), lo = fp16(a -
+// 2^11 hi), which is exact in FP32.  One instruction a value and plane, with
+// its rounding to FP16.
 __device__ __forceinline__ void split2(float a, float b, unsigned& hi, unsigned& lo) {
-  hi = __builtin_bit_cast(unsigned, h16x2{(_Float16)a, (_Float16)b});
-  __asm__("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "v"(a));
-  __asm__("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "v"(b));
+  const float down = 1.f / kSplitLow, up = -kSplitLow;
+  __asm__("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "=v"(hi) : "v"(a), "s"(down));
+  __asm__("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "+v"(hi) : "v"(b), "s"(down));
+  __asm__("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "s"(up), "v"(a));
+  __asm__("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "s"(up), "v"(b));
 }
 
 // ---- conv1 -> conv2 -> conv3 --------------------------------------------
@@ -81,7 +87,8 @@ __device__ __forceinline__ h16x8 ldw(const void* w, int blk, unsigned off) {
   return *reinterpret_cast<const h16x8*>(reinterpret_cast<const char*>(w) + blk * 1024 + off);
 }
 
-// One K step of a wavefront's tiles: w_lo x_hi and w_hi x_lo in sums of their own
+// One K step of a wavefront's tiles: w_lo x_hi and w_hi x_lo in sums of their
+// own, 2^11 times as large as they count
 template <int T, int NF>
 __device__ __forceinline__ void step(f32x4 (&acc)[T][NF], f32x4 (&low)[T][NF], const h16x8 (&w)[NF][2],
                                      const h16x8 (&x)[T][2]) {
@@ -134,7 +141,8 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[T][NF], const f32x
       float v[2];
 #pragma unroll
       for (int k = 0; k < 2; ++k)
-        v[k] = fmaxf(fmaf(acc[t][(e + k) >> 2][(e + k) & 3] + low[t][(e + k) >> 2][(e + k) & 3], sc[e + k], b[e + k]), 0.f);
+        v[k] = fmaxf(fmaf(fmaf(low[t][(e + k) >> 2][(e + k) & 3], 1.f / kSplitLow, acc[t][(e + k) >> 2][(e + k) & 3]),
+                          sc[e + k], b[e + k]), 0.f);
       unsigned h, l;
       split2(v[0], v[1], h, l);
       hi[e / 2] = h;
@@ -484,7 +492,8 @@ fc1_split_kernel(long long n, const unsigned char* __restrict__ X, const unsigne
     for (int i = 0; i < FN; ++i)
 #pragma unroll
       for (int j = 0; j < FM; ++j) {
-        acc[i][j] += low[i][j];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[i][j][q] = fmaf(low[i][j][q], 1.f / kSplitLow, acc[i][j][q]);
         tot[i][j] = z == st0 ? acc[i][j] : tot[i][j] + acc[i][j];
         acc[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
@@ -601,18 +610,19 @@ __global__ void __launch_bounds__(512) fc2_split_kernel(long long n, const float
   }
 }
 
-// W[N][K] FP32, row o times rs[o], as operand planes.  Rows are paired so that
+// W[N][K] FP32, row o times rs[o], as operand planes, the low one times `low`
+// (2^11; conv1's 1, whose planes share one sum).  Rows are paired so that
 // a lane's sums of two fragments are 8 consecutive channels: row r of fragment
 // f is channel 32 (f / 2) + 8 (r / 4) + 4 (f & 1) + r % 4.  Conv layers:
 // [K / 32][N / 16][plane][64 lanes][8]; fc1 (rows): [N][K / 32][plane][32].
 __global__ void split_weights_kernel(const float* __restrict__ w, const float* __restrict__ rs, int N, int K, int rows,
-                                     _Float16* __restrict__ out) {
+                                     float low, _Float16* __restrict__ out) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)N * K) return;
   const int row = (int)(i / K), k = (int)(i % K), f = row >> 4, r = row & 15;
   const int o = 32 * (f >> 1) + 8 * (r >> 2) + 4 * (f & 1) + (r & 3);
   const float v = w[(long long)o * K + k] * rs[o];
-  const _Float16 hi = (_Float16)v, lo = (_Float16)(v - (float)hi);
+  const _Float16 hi = (_Float16)v, lo = (_Float16)((v - (float)hi) * low);
   const int ks = k >> 5, g = (k >> 3) & 3, e = k & 7;
   _Float16* d = rows ? out + ((long long)row * (K / 32) + ks) * 64 + (k & 31)
                      : out + (((long long)ks * (N / 16) + f) * 2 * 64 + 16 * g + r) * 8 + e;
@@ -622,10 +632,10 @@ __global__ void split_weights_kernel(const float* __restrict__ w, const float* _
 
 }  // namespace
 
-void launch_split_weights(const float* w, const float* row_scale, int N, int K, bool rows, void* out, hipStream_t s) {
+void launch_split_weights(int layer, const float* w, const float* row_scale, int N, int K, void* out, hipStream_t s) {
   const long long n = (long long)N * K;
   hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, row_scale, N, K,
-                     rows ? 1 : 0, reinterpret_cast<_Float16*>(out));
+                     layer == 3 ? 1 : 0, layer == 0 ? 1.f : kSplitLow, reinterpret_cast<_Float16*>(out));
 }
 
 // Rules, with both sides measured (us; FP32 searches of A = 18 and A = 6, d = 1).

@@ -1,0 +1,66 @@
+"""The FP32 network on weights whose channels differ in size.  Multiplying a
+conv channel by 2^k and the next layer's weights on it by 2^-k changes no value
+of the network, in FP32 arithmetic not a bit of its outputs: the split form has
+to hold such channels as well as even ones.
+
+Tolerance: the operands carry 22 bits or more and the product left out is below
+2^-22 of a term, so a layer adds at most some 2^-22 of its values and four
+layers stay within 2^-20 of the largest |Q|."""
+import numpy as np
+import pytest
+
+from paper_2107_01715_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+NEXT = {"conv1": "conv2", "conv2": "conv3", "conv3": "fc1"}
+
+
+def _lib():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_01715_amd import bcts as lib
+    return lib
+
+
+def _exact(weights, stacks):
+    """Q in float64 by plain torch on the CPU."""
+    import torch
+    import torch.nn.functional as F
+    w = {k: torch.from_numpy(np.asarray(v)).double() for k, v in weights.items()}
+    x = torch.from_numpy(stacks).double() / 255.0
+    x = F.relu(F.conv2d(x, w["conv1.w"], w["conv1.b"], stride=4))
+    x = F.relu(F.conv2d(x, w["conv2.w"], w["conv2.b"], stride=2))
+    x = F.relu(F.conv2d(x, w["conv3.w"], w["conv3.b"]))
+    x = F.relu(F.linear(x.flatten(1), w["fc1.w"], w["fc1.b"]))
+    return F.linear(x, w["fc2.w"], w["fc2.b"]).numpy()
+
+
+def _scaled(weights, layer, channels, k):
+    """The same network, some of a layer's channels 2^k times as large."""
+    w = {name: np.array(v) for name, v in weights.items()}
+    w[layer + ".w"][channels] *= np.float32(2.0 ** k)
+    w[layer + ".b"][channels] *= np.float32(2.0 ** k)
+    nxt = w[NEXT[layer] + ".w"]
+    nxt.reshape(len(nxt), len(w[layer + ".b"]), -1)[:, channels] *= np.float32(2.0 ** -k)
+    return w
+
+
+def _q(lib, weights, stacks):
+    ctx = lib.Context(0)
+    ctx.set_qnet(W.qnet_blob(weights))
+    ctx.set_precision(lib.FP32)
+    q = ctx.debug_qnet(stacks, 18)
+    ctx.close()
+    return q
+
+
+@pytest.mark.parametrize("k", [4, 8])
+@pytest.mark.parametrize("layer", ["conv1", "conv2", "conv3"])
+def test_uneven_channels(layer, k):
+    lib = _lib()
+    weights = _scaled(W.qnet_weights(11), layer, [3], k)
+    stacks = W.roots(1400, 40)[1]
+    want = _exact(weights, stacks)
+    err = np.abs(_q(lib, weights, stacks) - want).max() / np.abs(want).max()
+    assert err <= 2.0 ** -20, err

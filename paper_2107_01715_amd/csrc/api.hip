@@ -27,6 +27,7 @@
 #include "../../include/bcts.h"
 #include "bcts_internal.h"
 #include "qnet_groups.h"
+#include "split_scales.h"
 #include "plan.h"
 #include "mlp_host.h"
 
@@ -375,51 +376,6 @@ bcts_status enqueue_level(bcts_ctx* c, const Plan& p, char* A, int k, const int3
     launch_render_kept(k, p.keep_count[k], lr, roots, reinterpret_cast<const int*>(A + p.o_keep[k]),
                        reinterpret_cast<uint8_t*>(A + p.o_pos[k]), frames, s);
   return BCTS_OK;
-}
-
-// Powers of two that bring the FP32 network's operands into FP16's range
-// (qnet_split.hip) and what they make of the accumulator scales and biases;
-// false when one is beyond 2^+-60 (weights or biases of a size no trained
-// network has), where the FP32 instruction runs.
-struct SplitScales {
-  std::vector<float> row[4], out[4], bias[4];
-};
-bool split_scales(const std::vector<float>* W, const std::vector<float>* B, SplitScales* sp) {
-  bool ok = true;
-  double bound = 255.0;          // of the layer's inputs, unscaled
-  int e_in = 0;                  // inputs are held times 2^e_in
-  for (int l = 0; l < 4; ++l) {
-    const size_t N = B[l].size(), K = W[l].size() / N;
-    const double acc = l == 0 ? 1.0 / 255.0 : 1.0;
-    std::vector<int> e_row(N, 0);
-    double top = 0.0;
-    for (size_t o = 0; o < N; ++o) {
-      double sum = 0.0, m = 0.0;
-      for (size_t k = 0; k < K; ++k) {
-        const double v = std::fabs((double)W[l][o * K + k]);
-        sum += v;
-        m = std::max(m, v);
-      }
-      top = std::max(top, sum * bound * acc + std::fabs((double)B[l][o]));
-      if (m > 0.0) e_row[o] = 13 - std::ilogb(m);
-    }
-    int e_out = 0;                // fc1's outputs stay FP32, unscaled
-    if (l < 3 && top > 0.0) e_out = 14 - std::ilogb(top);
-    ok = ok && std::abs(e_out) <= 60;
-    for (size_t o = 0; o < N; ++o) {
-      ok = ok && std::abs(e_row[o]) <= 60;
-      const int er = std::max(-60, std::min(60, e_row[o])), eo = std::max(-60, std::min(60, e_out));
-      sp->row[l].push_back((float)std::ldexp(1.0, er));
-      // conv1: 1/255 as the FP32 path multiplies it; a conv layer's outputs are
-      // split from 2^11 times what the planes hold
-      const double held = l < 3 ? (double)kSplitLow : 1.0;
-      sp->out[l].push_back((float)std::ldexp(held * (l == 0 ? (double)(1.f / 255.f) : 1.0), eo - er - e_in));
-      sp->bias[l].push_back((float)std::ldexp(held * (double)B[l][o], eo));
-    }
-    bound = top;
-    e_in = std::max(-60, std::min(60, e_out));
-  }
-  return ok;
 }
 
 // conv1 of a layer-path chunk by sibling groups (true) or stack by stack.
@@ -1242,13 +1198,13 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
   // the split planes (7 MB) stay out of what the budget counts: a search that
   // fitted a budget without them still does
   const size_t counted = o;
-  // scales of rows and layers, then per layer planes, row scales, output scales, biases
+  // per layer planes, row and column scales, output scales, biases
   SplitScales sp;
   c->q.split = split_scales(W, B, &sp);
-  size_t soff[4][4];
+  size_t soff[4][5];
   for (int l = 0; l < 4; ++l) {
     soff[l][0] = o; o += align_up(W[l].size() * 4);
-    for (int k = 1; k < 4; ++k) { soff[l][k] = o; o += align_up(B[l].size() * 4); }
+    for (int k = 1; k < 5; ++k) { soff[l][k] = o; o += align_up((k == 2 ? (size_t)NK[l][1] : B[l].size()) * 4); }
   }
   if (c->wmem) {
     HIPCHECK(c, hipStreamSynchronize(c->stream));
@@ -1287,15 +1243,17 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
       launch_fc1_weight_tiles(c->q.w8[l], const_cast<void*>(c->q.wf8[l]), NK[l][0], NK[l][1], 1, c->stream);
     }
   }
-  for (int l = 0; l < 4; ++l) {
-    const std::vector<float>* v[3] = {&sp.row[l], &sp.out[l], &sp.bias[l]};
-    for (int k = 0; k < 3; ++k)
+  for (int l = 0; l < 4 && c->q.split; ++l) {
+    const std::vector<float>* v[4] = {&sp.row[l], &sp.col[l], &sp.out[l], &sp.bias[l]};
+    for (int k = 0; k < 4; ++k)
       HIPCHECK(c, hipMemcpy(base + soff[l][k + 1], v[k]->data(), v[k]->size() * 4, hipMemcpyHostToDevice));
-    launch_split_weights(l, c->q.w[l], reinterpret_cast<const float*>(base + soff[l][1]), NK[l][0], NK[l][1],
+    const float* scales[4];
+    for (int k = 0; k < 4; ++k) scales[k] = reinterpret_cast<const float*>(base + soff[l][k + 1]);
+    launch_split_weights(l, c->q.w[l], scales[0], scales[1], (int)sp.col[l].size(), NK[l][0], NK[l][1],
                          base + soff[l][0], c->stream);
     c->q.wsplit[l] = base + soff[l][0];
-    c->q.ssplit[l] = reinterpret_cast<const float*>(base + soff[l][2]);
-    c->q.bsplit[l] = reinterpret_cast<const float*>(base + soff[l][3]);
+    c->q.ssplit[l] = scales[2];
+    c->q.bsplit[l] = scales[3];
   }
   // activation scales until calibrated: pixels 1:1 (255 -> 256 in e4m3), others unit
   c->q.ascale[0] = 1.f;

@@ -90,10 +90,11 @@ struct QnetDev {
   const void* wfb[5];          // bf16
   const void* wf8[5];          // e4m3
   const void* wf8k[5];         // e4m3, conv2 / conv3 for the K = 128 instruction (launch_fragment_major_k128)
-  // conv1..fc1 as two FP16 planes each, rows scaled by powers of two (see
-  // launch_split_weights); layer output = ReLU(sum ssplit[o] + bsplit[o]),
-  // the conv layers' in the scale of their splits, fc1's in its own.
-  // split false: a scale is out of range, FP32 runs on the FP32 instruction.
+  // conv1..fc1 as two FP16 planes each, rows and input channels scaled by
+  // powers of two (see launch_split_weights); layer output = ReLU(sum ssplit[o]
+  // + bsplit[o]), the conv layers' each channel in the scale of its split,
+  // fc1's in its own.  split false: the planes would hold too few bits of these
+  // weights (see split_scales.cpp), FP32 runs on the FP32 instruction.
   bool split;
   const void* wsplit[4];
   const float *ssplit[4], *bsplit[4];
@@ -164,8 +165,9 @@ struct SplitConvArgs {
   const float *scale[3], *bias[3];
   unsigned char* x3;           // [stacks][98][2][32] FP16
 };
-constexpr float kSplitLow = 2048.f;                     // a low plane's factor, and the held outputs'
-void launch_split_weights(int layer, const float* w, const float* row_scale, int N, int K, void* out, hipStream_t s);
+// col_scale: of the weights on each of C input channels, k % C of weight k
+void launch_split_weights(int layer, const float* w, const float* row_scale, const float* col_scale, int C, int N, int K,
+                          void* out, hipStream_t s);
 
 // Copies fc1's W[N][K] (N a multiple of 256, eb bytes per element) into
 // stage-major tiles.

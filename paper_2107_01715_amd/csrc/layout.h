@@ -37,6 +37,8 @@ inline long long fc1_padded_rows(long long n) { return (n + kFc1Rows - 1) / kFc1
 
 // K slices of the FP32 fc1 (its 98 K stages of 32 split evenly).
 constexpr int kFc1Split = 7;
+// FP32 in split FP16: factor of a low plane, and of a conv output before its split
+constexpr float kSplitLow = 2048.f;
 
 // Precisions (mirrors bcts_precision).
 enum Prec { P_FP32 = 0, P_BF16 = 1, P_FP8 = 2 };

@@ -19,13 +19,15 @@
 // layer-by-layer kernels on v_mfma_f32_16x16x4_f32 took 5.86 (the FP32
 // instruction alone 4.2 at the card's 154 TFLOP/s), fc1 0.56 (1.65).
 //
-// Scaling is by powers of two, exact: a row of weights by the one that brings
-// its largest into [2^13, 2^14); a layer's outputs by the one that brings the
-// bound max_o(sum |w_o| bound_in + |b_o|) to at most 2^15.  FP16's normal values
-// end at 2^-14 and the low plane is held 2^11 times as large, so a value keeps
-// its 22 bits down to 2^-29 of the bound (2^-17 with the low plane as it is,
-// which the median positive output of conv3 passes: the bound grows with each
-// layer).  conv1's planes share one sum, its low one is held as it is.
+// Scaling is by powers of two, exact, a power for every output channel and every
+// row of weights (split_scales.cpp): a channel's outputs are held with what it can
+// reach at most at 2^14 to 2^15, the next layer's weights on it divided by the
+// same.  FP16's normal values end at 2^-14 and the low plane is held 2^11 times as
+// large, so a value keeps its 22 bits down to 2^-29 of that bound (2^-17 with the
+// low plane as it is; the median positive output of conv3 lies at 2^-15, since the
+// bound grows with each layer).  conv1's planes share one sum, its low one is held
+// as it is.  Weights of which the planes would hold too few bits run on the FP32
+// instruction (qnet.hip).
 #include "bcts_internal.h"
 #include "qnet_groups.h"
 
@@ -610,18 +612,19 @@ __global__ void __launch_bounds__(512) fc2_split_kernel(long long n, const float
   }
 }
 
-// W[N][K] FP32, row o times rs[o], as operand planes, the low one times `low`
+// W[N][K] FP32, row o times rs[o], weight k times cs[k % C], as operand planes, the low one times `low`
 // (2^11; conv1's 1, whose planes share one sum).  Rows are paired so that
 // a lane's sums of two fragments are 8 consecutive channels: row r of fragment
 // f is channel 32 (f / 2) + 8 (r / 4) + 4 (f & 1) + r % 4.  Conv layers:
 // [K / 32][N / 16][plane][64 lanes][8]; fc1 (rows): [N][K / 32][plane][32].
-__global__ void split_weights_kernel(const float* __restrict__ w, const float* __restrict__ rs, int N, int K, int rows,
-                                     float low, _Float16* __restrict__ out) {
+__global__ void split_weights_kernel(const float* __restrict__ w, const float* __restrict__ rs,
+                                     const float* __restrict__ cs, int C, int N, int K, int rows, float low,
+                                     _Float16* __restrict__ out) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long long)N * K) return;
   const int row = (int)(i / K), k = (int)(i % K), f = row >> 4, r = row & 15;
   const int o = 32 * (f >> 1) + 8 * (r >> 2) + 4 * (f & 1) + (r & 3);
-  const float v = w[(long long)o * K + k] * rs[o];
+  const float v = w[(long long)o * K + k] * (cs[k % C] * rs[o]);
   const _Float16 hi = (_Float16)v, lo = (_Float16)((v - (float)hi) * low);
   const int ks = k >> 5, g = (k >> 3) & 3, e = k & 7;
   _Float16* d = rows ? out + ((long long)row * (K / 32) + ks) * 64 + (k & 31)
@@ -632,10 +635,11 @@ __global__ void split_weights_kernel(const float* __restrict__ w, const float* _
 
 }  // namespace
 
-void launch_split_weights(int layer, const float* w, const float* row_scale, int N, int K, void* out, hipStream_t s) {
+void launch_split_weights(int layer, const float* w, const float* row_scale, const float* col_scale, int C, int N, int K,
+                          void* out, hipStream_t s) {
   const long long n = (long long)N * K;
-  hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, row_scale, N, K,
-                     layer == 3 ? 1 : 0, layer == 0 ? 1.f : kSplitLow, reinterpret_cast<_Float16*>(out));
+  hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, row_scale, col_scale,
+                     C, N, K, layer == 3 ? 1 : 0, layer == 0 ? 1.f : kSplitLow, reinterpret_cast<_Float16*>(out));
 }
 
 // Rules, with both sides measured (us; FP32 searches of A = 18 and A = 6, d = 1).

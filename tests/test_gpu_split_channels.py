@@ -55,11 +55,52 @@ def _q(lib, weights, stacks):
     return q
 
 
-@pytest.mark.parametrize("k", [4, 8])
+@pytest.mark.parametrize("k", [4, 8, 12, 20, 40, -20])
 @pytest.mark.parametrize("layer", ["conv1", "conv2", "conv3"])
 def test_uneven_channels(layer, k):
     lib = _lib()
     weights = _scaled(W.qnet_weights(11), layer, [3], k)
+    stacks = W.roots(1400, 40)[1]
+    want = _exact(weights, stacks)
+    err = np.abs(_q(lib, weights, stacks) - want).max() / np.abs(want).max()
+    assert err <= 2.0 ** -20, err
+
+
+def test_powers_of_two_change_no_bit():
+    """Every layer's channels in sizes 2^-12..2^12, in searches too."""
+    lib = _lib()
+    base = W.qnet_weights(11)
+    weights, rng = base, np.random.default_rng(5)
+    for layer in ("conv1", "conv2", "conv3"):
+        for c in range(len(base[layer + ".b"])):
+            weights = _scaled(weights, layer, [c], int(rng.integers(-12, 13)))
+    pos, stacks = W.roots(1401, 24)
+    ep = W.env_params(7)
+    got = []
+    for w in (base, weights):
+        ctx = lib.Context(0)
+        ctx.set_env(ep.delta, ep.vel)
+        ctx.set_qnet(W.qnet_blob(w))
+        out = [ctx.debug_qnet(stacks, 18)]
+        for prec in (lib.FP32, lib.BF16):                   # BF16: the correction's evaluations are FP32's
+            ctx.set_precision(prec)
+            out += list(ctx.search(pos, stacks, 2, 6, 0.99, lib.correction(True)))
+        ctx.close()
+        got.append(out)
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("layer", ["conv1", "conv2"])
+def test_a_channel_that_never_fires(layer):
+    """One channel 2^36 times as large with a bias that keeps it at zero on
+    every stack met here, the next layer's weights on it as they are: what
+    could be is far above what is, and the bits go to what is."""
+    lib = _lib()
+    weights = {k: np.array(v) for k, v in W.qnet_weights(11).items()}
+    weights[layer + ".w"][3] *= np.float32(2.0 ** 36)
+    reach = np.maximum(weights[layer + ".w"][3], 0).sum() * (1 if layer == "conv1" else 2)
+    weights[layer + ".b"][3] = -0.75 * reach
     stacks = W.roots(1400, 40)[1]
     want = _exact(weights, stacks)
     err = np.abs(_q(lib, weights, stacks) - want).max() / np.abs(want).max()

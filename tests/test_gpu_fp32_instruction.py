@@ -1,0 +1,94 @@
+"""FP32 on the FP32 matrix instruction, where the weights' scales are past what
+the split form takes: conv2's weights 2^80 times as large and conv3's 2^-80
+times, which changes no value of the network."""
+import numpy as np
+import pytest
+
+from oracle import env as E, qnet as Q, search as S
+from paper_2107_01715_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+GAMMA, RTOL = 0.99, 1e-5                                    # the FP32 bar against the oracle
+
+
+def _far_weights():
+    w = {k: np.array(v) for k, v in W.qnet_weights(7).items()}
+    w["conv2.w"] *= np.float32(2.0 ** 80)
+    w["conv2.b"] *= np.float32(2.0 ** 80)
+    w["conv3.w"] *= np.float32(2.0 ** -80)
+    return w
+
+
+@pytest.fixture(scope="module")
+def setup():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2107_01715_amd import bcts as lib
+    ep = W.env_params(1001)
+    ctx = lib.Context(0)
+    ctx.set_env(ep.delta, ep.vel)
+    ctx.set_qnet(W.qnet_blob(_far_weights()))
+    yield lib, ctx, S.World(ep.delta, ep.vel, Q.prepare(W.qnet_weights(7)))
+    ctx.close()
+
+
+def test_not_the_split_form(setup):
+    lib, ctx, _ = setup
+    other = lib.Context(0)
+    other.set_qnet(W.qnet_blob(W.qnet_weights(7)))
+    stacks = W.roots(11, 40)[1]
+    assert not np.array_equal(ctx.debug_qnet(stacks, 18), other.debug_qnet(stacks, 18))
+    other.close()
+
+
+@pytest.mark.parametrize("A,parents,group", [(18, 3, 18), (6, 5, 6), (4, 7, 4), (5, 3, 4)])
+def test_sibling_groups(setup, A, parents, group):
+    """conv1 by sibling groups, the last group ragged, against the oracle and
+    against stack by stack."""
+    lib, ctx, world = setup
+    pos, st = W.roots(3300 + A, parents)
+    x = np.stack([E.step(pos[r], st[r], a, world.delta, world.vel)[1] for r in range(parents) for a in range(group)]
+                 + ([st[0]] if group != A else []))
+    ctx.set_precision(lib.FP32)
+    try:
+        ctx.set_tuning(lib.TUNE_CONV1_GROUPS, 2)
+        got = ctx.debug_qnet_siblings(x, 18, group)
+        want = Q.qvalues(x, world.w64, 18)
+        err = np.abs(got - want).max(axis=1)
+        assert (err <= RTOL * np.abs(want).max(axis=1) + 1e-6).all(), (err / np.abs(want).max(axis=1)).max()
+        ctx.set_tuning(lib.TUNE_CONV1_GROUPS, 0)
+        assert np.array_equal(got, ctx.debug_qnet_siblings(x, 18, group))
+        assert np.array_equal(got, ctx.debug_qnet(x, 18))
+    finally:
+        ctx.set_tuning(lib.TUNE_CONV1_GROUPS, 1)
+
+
+@pytest.mark.parametrize("prec", ["FP32", "BF16"])
+def test_searches(setup, prec):
+    """Whole searches, conv1 by groups, per stack and as chosen, in small
+    chunks: the same bits (BF16: its FP32 evaluations of the correction), and
+    FP32 at the oracle's bar."""
+    lib, ctx, world = setup
+    A, d = W.mixed_shapes(1006, 60, (4, 6, 18), (1, 2, 3))
+    pos, st = W.roots(1006, 60)
+    corr, chunk = lib.correction(True, 1.0), ctx.get_tuning(lib.TUNE_LAYER_CHUNK)
+    ctx.set_precision(getattr(lib, prec))
+    try:
+        ctx.set_tuning(lib.TUNE_LAYER_CHUNK, 1000)
+        out = []
+        for groups in (2, 0, 1):
+            ctx.set_tuning(lib.TUNE_CONV1_GROUPS, groups)
+            out.append(ctx.search_batch(pos, st, d, A, GAMMA, corr))
+        for act, q in out[1:]:
+            assert np.array_equal(out[0][0], act) and np.array_equal(out[0][1], q)
+        if prec == "FP32":
+            for r in np.flatnonzero(A.astype(np.int64) ** d <= 324)[:6]:
+                ref = S.search(world, pos[r], st[r], int(d[r]), int(A[r]), GAMMA, correction=True, c=1.0)
+                err = np.abs(out[0][1][r][:A[r]] - np.asarray(ref.q)).max()
+                assert err <= RTOL * np.abs(ref.q).max() + 1e-7, (r, err)
+                assert out[0][0][r] == ref.action or out[0][0][r] in ref.ties
+    finally:
+        ctx.set_tuning(lib.TUNE_CONV1_GROUPS, 1)
+        ctx.set_tuning(lib.TUNE_LAYER_CHUNK, chunk)
+        ctx.set_precision(lib.FP32)

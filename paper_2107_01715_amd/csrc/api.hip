@@ -536,7 +536,7 @@ bcts_status enqueue_search_at(bcts_ctx* c, const Plan& p, char* A, const int32_t
     c->t_items = p.n_items;
     c->t_tail = !p.tail_chunks.empty();
     c->t_conv1_groups = 0;
-    if (!p.fused)
+    if (!p.fused && !(c->prec == P_FP32 && c->q.split))       // split FP16 has no such choice
       for (const auto& ch : p.chunks) c->t_conv1_groups += conv1_by_groups(c, ch) ? 1 : 0;
     c->t_nodes = 0;
     for (int k = 1; k <= p.maxd; ++k) c->t_nodes += p.lvl_count[k];

@@ -92,3 +92,23 @@ def test_searches(setup, prec):
         ctx.set_tuning(lib.TUNE_CONV1_GROUPS, 1)
         ctx.set_tuning(lib.TUNE_LAYER_CHUNK, chunk)
         ctx.set_precision(lib.FP32)
+
+
+def test_timing_counts_conv1_groups_where_they_ran(setup):
+    """out[20]: chunks whose conv1 ran by sibling groups, none where the split
+    form ran."""
+    lib, far, _ = setup
+    split = lib.Context(0)
+    ep = W.env_params(1001)
+    split.set_env(ep.delta, ep.vel)
+    split.set_qnet(W.qnet_blob(W.qnet_weights(7)))
+    pos, st = W.roots(1006, 4)
+    for ctx, want in ((far, 1.0), (split, 0.0)):
+        ctx.set_precision(lib.FP32)
+        ctx.set_tuning(lib.TUNE_CONV1_GROUPS, 2)
+        ctx.set_timing(True)
+        ctx.search(pos, st, 2, 6, GAMMA, lib.correction(True))
+        assert ctx.get_timing()[20] == want
+        ctx.set_timing(False)
+        ctx.set_tuning(lib.TUNE_CONV1_GROUPS, 1)
+    split.close()

@@ -107,8 +107,7 @@ typedef struct {
 typedef struct bcts_ctx bcts_ctx;
 
 /* Create a context on HIP device `hip_device`.  hbm_budget_bytes caps the
- * device memory the context may hold (0 = 80% of the device's free memory;
- * 7 MB of weight copies for the FP32 network come on top).
+ * device memory the context may hold (0 = 80% of the device's free memory).
  * BCTS_E_HIP if the device cannot be used.                                 */
 bcts_status bcts_create(int hip_device, size_t hbm_budget_bytes, bcts_ctx** out);
 void bcts_destroy(bcts_ctx* ctx);

@@ -65,6 +65,7 @@ struct bcts_ctx {
   // weights
   void* wmem = nullptr;
   size_t wbytes = 0;
+  char* wpin = nullptr;                 // the FP32 weights of a network in split FP16 (kPinnedWeights bytes)
   QnetDev q{};
   float wabs[5] = {0};
   bool fp8_calibrated = false;
@@ -150,6 +151,11 @@ bcts_status check_usable(bcts_ctx* c) {
   c->err.clear();
   return BCTS_OK;
 }
+
+// conv1..fc2 in FP32 (fc2's rows padded to 32), then the scales of the split
+// form's rows and input channels
+constexpr size_t kPinnedWeights = 4 * (32 * 256 + 64 * 512 + 64 * 576 + 512 * 3136 + 32 * 512 + (32 + 64 + 64 + 512) +
+                                       (256 + 32 + 64 + 64));
 
 // Staging memory that kernels write results to: coherent, so that the host
 // sees them once an event after the kernel has completed.
@@ -1082,6 +1088,7 @@ void bcts_destroy(bcts_ctx* c) {
   if (c->arena) (void)hipFree(c->arena);
   if (c->wmem) (void)hipFree(c->wmem);
   if (c->mlp_mem) (void)hipFree(c->mlp_mem);
+  if (c->wpin) (void)hipHostFree(c->wpin);
   if (c->pinned) (void)hipHostFree(c->pinned);
   for (int b = 0; b < 2; ++b) {
     if (c->tpin_ev[b]) (void)hipEventSynchronize(c->tpin_ev[b]);
@@ -1182,11 +1189,15 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
   std::memcpy(B[4].data(), f2b, sizeof(float) * 18);
 
   // fp32 w, bf16 w, fp8 w, bias, and for conv2 / conv3 fragment-major (fc1: stage-major tiled)
-  // bf16 and fp8 copies
+  // bf16 and fp8 copies.  A network in split FP16 has its planes in the FP32
+  // weights' place: those, which the FP8 calibration alone reads then, lie in
+  // pinned host memory, and the device holds no more than without the planes.
+  SplitScales sp;
+  const bool split = split_scales(W, B, &sp);
   size_t off[5][7], o = 0;
   for (int l = 0; l < 5; ++l) {
     const size_t n = W[l].size();
-    off[l][0] = o; o += align_up(n * 4);
+    off[l][0] = o; o += split ? 0 : align_up(n * 4);
     off[l][1] = o; o += align_up(n * 2);
     off[l][2] = o; o += align_up(n);
     off[l][3] = o; o += align_up(B[l].size() * 4);
@@ -1195,16 +1206,16 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
     off[l][5] = o; o += (l == 1 || l == 2) ? align_up(n) : l == 3 ? align_up(fc1_tiles * fc1_tile_bytes(1)) : 0;
     off[l][6] = o; o += (l == 1 || l == 2) ? align_up(n) : 0;        // FP8 for the K = 128 instruction
   }
-  // the split planes (7 MB) stay out of what the budget counts: a search that
-  // fitted a budget without them still does
-  const size_t counted = o;
-  // per layer planes, row and column scales, output scales, biases
-  SplitScales sp;
-  c->q.split = split_scales(W, B, &sp);
-  size_t soff[4][5];
-  for (int l = 0; l < 4; ++l) {
-    soff[l][0] = o; o += align_up(W[l].size() * 4);
-    for (int k = 1; k < 5; ++k) { soff[l][k] = o; o += align_up((k == 2 ? (size_t)NK[l][1] : B[l].size()) * 4); }
+  // split: per layer planes, output scales and (conv) biases; fc2's FP32 rows
+  size_t soff[4][3], fc2_off = o;
+  if (split) {
+    for (int l = 0; l < 4; ++l) {
+      soff[l][0] = o; o += align_up(W[l].size() * 4);
+      soff[l][1] = o; o += align_up(B[l].size() * 4);
+      soff[l][2] = o; o += l < 3 ? align_up(B[l].size() * 4) : 0;
+    }
+    fc2_off = o; o += align_up((size_t)kMaxA * NK[4][1] * 4);
+    if (!c->wpin) HIPCHECK(c, hipHostMalloc((void**)&c->wpin, kPinnedWeights, kPinnedFlags));
   }
   if (c->wmem) {
     HIPCHECK(c, hipStreamSynchronize(c->stream));
@@ -1212,12 +1223,16 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
     c->wmem = nullptr;
   }
   HIPCHECK(c, hipMalloc(&c->wmem, o));
-  c->wbytes = counted;
-  char* base = static_cast<char*>(c->wmem);
+  c->wbytes = o;
+  c->q.split = split;
+  char *base = static_cast<char*>(c->wmem), *pin = c->wpin;
   for (int l = 0; l < 5; ++l) {
-    HIPCHECK(c, hipMemcpy(base + off[l][0], W[l].data(), W[l].size() * 4, hipMemcpyHostToDevice));
+    char* w32 = split ? pin : base + off[l][0];
+    if (split) std::memcpy(w32, W[l].data(), W[l].size() * 4);
+    else HIPCHECK(c, hipMemcpy(w32, W[l].data(), W[l].size() * 4, hipMemcpyHostToDevice));
+    pin += split ? W[l].size() * 4 : 0;
     HIPCHECK(c, hipMemcpy(base + off[l][3], B[l].data(), B[l].size() * 4, hipMemcpyHostToDevice));
-    c->q.w[l] = reinterpret_cast<const float*>(base + off[l][0]);
+    c->q.w[l] = reinterpret_cast<const float*>(w32);
     c->q.wb[l] = reinterpret_cast<const uint16_t*>(base + off[l][1]);
     c->q.w8[l] = reinterpret_cast<const uint8_t*>(base + off[l][2]);
     c->q.b[l] = reinterpret_cast<const float*>(base + off[l][3]);
@@ -1243,17 +1258,27 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
       launch_fc1_weight_tiles(c->q.w8[l], const_cast<void*>(c->q.wf8[l]), NK[l][0], NK[l][1], 1, c->stream);
     }
   }
-  for (int l = 0; l < 4 && c->q.split; ++l) {
-    const std::vector<float>* v[4] = {&sp.row[l], &sp.col[l], &sp.out[l], &sp.bias[l]};
-    for (int k = 0; k < 4; ++k)
-      HIPCHECK(c, hipMemcpy(base + soff[l][k + 1], v[k]->data(), v[k]->size() * 4, hipMemcpyHostToDevice));
-    const float* scales[4];
-    for (int k = 0; k < 4; ++k) scales[k] = reinterpret_cast<const float*>(base + soff[l][k + 1]);
-    launch_split_weights(l, c->q.w[l], scales[0], scales[1], (int)sp.col[l].size(), NK[l][0], NK[l][1],
-                         base + soff[l][0], c->stream);
-    c->q.wsplit[l] = base + soff[l][0];
-    c->q.ssplit[l] = scales[2];
-    c->q.bsplit[l] = scales[3];
+  if (split) {
+    auto pinned = [&](const std::vector<float>& v) {
+      std::memcpy(pin, v.data(), v.size() * 4);
+      pin += v.size() * 4;
+      return reinterpret_cast<const float*>(pin) - v.size();
+    };
+    auto device = [&](const std::vector<float>& v, size_t at) {
+      (void)hipMemcpy(base + at, v.data(), v.size() * 4, hipMemcpyHostToDevice);
+      return reinterpret_cast<const float*>(base + at);
+    };
+    for (int l = 0; l < 4; ++l) {
+      const float *row = pinned(sp.row[l]), *col = pinned(sp.col[l]);
+      launch_split_weights(l, c->q.w[l], row, col, (int)sp.col[l].size(), NK[l][0], NK[l][1], base + soff[l][0],
+                           c->stream);
+      c->q.wsplit[l] = base + soff[l][0];
+      c->q.ssplit[l] = device(sp.out[l], soff[l][1]);
+      c->q.bsplit[l] = l < 3 ? device(sp.bias[l], soff[l][2]) : c->q.b[3];   // fc1's outputs are not scaled
+    }
+    W[4].resize((size_t)kMaxA * NK[4][1]);
+    c->q.w2split = device(W[4], fc2_off);
+    HIPCHECK(c, hipGetLastError());
   }
   // activation scales until calibrated: pixels 1:1 (255 -> 256 in e4m3), others unit
   c->q.ascale[0] = 1.f;
@@ -1303,10 +1328,15 @@ bcts_status bcts_calibrate_fp8(bcts_ctx* c, int32_t n, const uint8_t* stacks) {
   bcts_correction off{0, 0.f, 0};
   Plan p;
   make_plan(p, n, dep.data(), Av.data(), 1.f, off, kMaxA, n, P_FP32, true);
-  const size_t maxb = p.total + 64;
-  st = ensure_arena(c, maxb);
+  // the FP32 weights of a network in split FP16 are copied beside the plan where
+  // the budget has room, and read from host memory where it has not
+  const size_t maxb = p.total + 64, w_at = align_up(maxb), w_bytes = c->q.split ? kPinnedWeights : 0;
+  st = ensure_arena(c, w_bytes > 0 ? w_at + w_bytes : maxb);
+  const bool copied = w_bytes > 0 && st == BCTS_OK;
+  if (w_bytes > 0 && st == BCTS_E_NOMEM && (st = ensure_arena(c, maxb)) == BCTS_OK) c->err.clear();
   if (st != BCTS_OK) return st;
   hipStream_t s = c->stream;
+  QnetDev q = c->q;
   st = upload_tables(c, p, s);
   if (st != BCTS_OK) return st;
   HIPCHECK(c, hipMemcpyAsync(c->arena + p.o_root_stack, stacks, (size_t)n * 4 * kFrameBytes,
@@ -1317,7 +1347,12 @@ bcts_status bcts_calibrate_fp8(bcts_ctx* c, int32_t n, const uint8_t* stacks) {
   launch_item_desc(0, n, reinterpret_cast<const Seg*>(c->arena + p.o_segs), (int)p.segs.size(),
                    reinterpret_cast<const RootInfo*>(c->arena + p.o_roots), fb, desc, s);
   float* ws = reinterpret_cast<float*>(c->arena + p.o_ws);
-  launch_qnet(P_FP32, c->q, desc, n, ws, reinterpret_cast<float*>(c->arena + p.o_V),
+  if (copied) {
+    HIPCHECK(c, hipMemcpyAsync(c->arena + w_at, c->wpin, w_bytes, hipMemcpyHostToDevice, s));
+    for (int l = 0; l < 5; ++l)
+      q.w[l] = reinterpret_cast<const float*>(c->arena + w_at) + (c->q.w[l] - reinterpret_cast<const float*>(c->wpin));
+  }
+  launch_qnet(P_FP32, q, desc, n, ws, reinterpret_cast<float*>(c->arena + p.o_V),
               reinterpret_cast<float*>(c->arena + p.o_q0), s);
   // absmax of each layer's FP32 input: x1, x2, x3, h
   float* mx = reinterpret_cast<float*>(c->arena + p.total);

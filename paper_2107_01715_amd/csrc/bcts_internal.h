@@ -98,6 +98,7 @@ struct QnetDev {
   bool split;
   const void* wsplit[4];
   const float *ssplit[4], *bsplit[4];
+  const float* w2split;        // fc2's rows [kMaxA][512] in FP32
 };
 
 // Learned forward-model world: weights on the device, FP32.  The four layers

@@ -549,7 +549,7 @@ __global__ void __launch_bounds__(512) fc2_split_kernel(long long n, const float
   for (int j = 0; j < 4; ++j) {
     const int k = 64 * c + 16 * j + 4 * g;
     w[0][j] = *reinterpret_cast<const f32x4*>(W2 + r16 * 512 + k);
-    w[1][j] = *reinterpret_cast<const f32x4*>(W2 + (16 + r16) * 512 + k);
+    w[1][j] = *reinterpret_cast<const f32x4*>(W2 + (16 + r16 < kMaxA ? 16 + r16 : kMaxA - 1) * 512 + k);   // rows past the last: unused
   }
   if constexpr (SLICES) {
     f32x4 p[kFc1Split][4], sc[4], b[4];                    // every load in flight at once
@@ -708,10 +708,10 @@ void launch_qnet_split(const QnetDev& q, const ItemDesc* desc, long long n, cons
   if (ev) (void)hipEventRecord(ev[4], s);
   if (slices)
     hipLaunchKernelGGL((fc2_split_kernel<true, 4>), dim3((unsigned)((n + 3) / 4)), dim3(512), 0, s, n, part,
-                       q.ssplit[3], q.bsplit[3], q.w[4], q.b[4], desc, V, q0);
+                       q.ssplit[3], q.bsplit[3], q.w2split, q.b[4], desc, V, q0);
   else
     hipLaunchKernelGGL((fc2_split_kernel<false, 16>), dim3((unsigned)((n + 15) / 16)), dim3(512), 0, s, n, h,
-                       q.ssplit[3], q.bsplit[3], q.w[4], q.b[4], desc, V, q0);
+                       q.ssplit[3], q.bsplit[3], q.w2split, q.b[4], desc, V, q0);
   if (ev) (void)hipEventRecord(ev[5], s);
 }
 

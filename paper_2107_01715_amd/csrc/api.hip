@@ -1219,8 +1219,10 @@ bcts_status bcts_set_qnet(bcts_ctx* c, const float* blob, size_t n_floats) {
   }
   if (c->wmem) {
     HIPCHECK(c, hipStreamSynchronize(c->stream));
+    c->qnet_set = false;                          // until the new weights are there
     HIPCHECK(c, hipFree(c->wmem));
     c->wmem = nullptr;
+    c->wbytes = 0;
   }
   HIPCHECK(c, hipMalloc(&c->wmem, o));
   c->wbytes = o;

@@ -41,7 +41,7 @@ bool split_scales(const std::vector<float>* W, const std::vector<float>* B, Spli
   for (int l = 0; l < 4; ++l) {
     const size_t N = B[l].size(), K = W[l].size() / N, C = bound.size();
     const double acc = l == 0 ? (double)(1.f / 255.f) : 1.0;   // as the FP32 path multiplies it
-    std::vector<double> col(C), squares(C, 0.0);
+    std::vector<double> col(C), readers(C, 0.0);   // readers: sum over the rows of their largest weight's square
     double held = 0.0;                           // sum over a row of the typical inputs' squares, as held
     for (size_t c = 0; c < C; ++c) {
       col[c] = bound[c] > 0.0 ? std::ldexp(1.0, -e_in[c]) : 0.0;   // a channel that is always zero
@@ -50,20 +50,20 @@ bool split_scales(const std::vector<float>* W, const std::vector<float>* B, Spli
     }
     std::vector<double> b_out(N), t_out(N), d_out(N);
     std::vector<int> e_out(N, 0);
-    std::vector<double> sum(C), positive(C), most(C), largest(C), part;
+    std::vector<double> part;
+    float sum[256], positive[256], most[256], largest[256];
     for (size_t o = 0; o < N; ++o) {
       const float* w = &W[l][o * K];
       const double bias = B[l][o];
-      // of the row's weights on each channel
-      for (size_t c = 0; c < C; ++c) sum[c] = positive[c] = most[c] = largest[c] = 0.0;
+      // of the row's weights on each channel (a lane a channel: 1.6 M weights in fc1)
+      for (size_t c = 0; c < C; ++c) sum[c] = positive[c] = most[c] = largest[c] = 0.f;
       for (size_t k = 0; k < K; k += C)
         for (size_t c = 0; c < C; ++c) {
-          const double v = w[k + c], up = v > 0.0 ? v : 0.0, size = std::fabs(v);
+          const float v = w[k + c], up = v > 0.f ? v : 0.f, size = std::fabs(v);
           sum[c] += v;
           positive[c] += up;
           most[c] = most[c] > up ? most[c] : up;
           largest[c] = largest[c] > size ? largest[c] : size;
-          squares[c] += v * v;
         }
       double top = 0.0, reach = 0.0, at_dark = 0.0;
       part.clear();
@@ -71,7 +71,8 @@ bool split_scales(const std::vector<float>* W, const std::vector<float>* B, Spli
         top = std::max(top, largest[c] * col[c]);
         reach += positive[c] * bound[c];
         at_dark += sum[c] * dark[c];
-        if (most[c] * typical[c] > 0.0) part.push_back(most[c] * typical[c]);
+        readers[c] += (double)largest[c] * largest[c];
+        if (most[c] > 0.f && typical[c] > 0.0) part.push_back(most[c] * typical[c]);
       }
       b_out[o] = std::max(0.0, reach * acc + bias);
       if (b_out[o] == 0.0) {                     // never positive: zeros
@@ -104,8 +105,8 @@ bool split_scales(const std::vector<float>* W, const std::vector<float>* B, Spli
     double values = 0.0, errors = 0.0;           // of the layer's inputs on a dark stack
     for (size_t c = 0; c < C; ++c) {
       if (dark[c] == 0.0) continue;              // held without error
-      values += squares[c] * dark[c] * dark[c];
-      errors += squares[c] * std::pow(fine * col[c], 2.0);
+      values += readers[c] * dark[c] * dark[c];
+      errors += readers[c] * std::pow(fine * col[c], 2.0);
     }
     if (errors > std::pow(4.0 * need, 2.0) * values) return false;
     bound = b_out;

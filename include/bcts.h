@@ -218,13 +218,19 @@ void bcts_graph_destroy(bcts_graph* graph);
  * precision; every choice keeps each stack's sum order fixed):
  *   BCTS_TUNE_FUSED        1 = BF16/FP8 run conv1..conv3 fused per sibling
  *                          group (default), 0 = layer-by-layer kernels.
-                          FP32 has one form: conv1..conv3 in one kernel,
-                          every operand the sum of two FP16 values on the
-                          FP16 matrix instruction (its error against 64
-                          bits is below the FP32 instruction's), or, where
-                          weights leave the range that form can scale (a
-                          row or layer past 2^+-60), layer by layer on the
-                          FP32 instruction
+ *                          FP32 does not read it: conv1..conv3 run in one
+ *                          kernel, every operand the sum of two FP16 values
+ *                          (22 bits or more, every channel and row of
+ *                          weights with a power of two of its own) on the
+ *                          FP16 matrix instruction, or layer by layer on the
+ *                          FP32 instruction where bcts_set_qnet computes
+ *                          that the two values would lose bits: weights or
+ *                          biases past 2^+-60, inputs of a layer that could
+ *                          be far larger than they are, a row with one
+ *                          weight far above its others.  Against 64 bits the
+ *                          first form was half as far off as the second on
+ *                          the networks measured (Kaiming and heavy-tailed
+ *                          weights, channels of even and uneven size)
  *   BCTS_TUNE_FUSED_ROUND  stacks per LDS round of the fused kernel: 1..4
  *                          (BF16 caps at 3: a round of 4 exceeds the LDS)
  *   BCTS_TUNE_FUSED_CHUNK  stacks per Q-network chunk on the fused path

@@ -124,7 +124,7 @@ struct MlpDev {
   const float *w1a, *b1, *b2, *b3, *bo, *bqp;            // rows of kMlpPad (bqp: 16 kMlpHeadFrags)
   const float *wq, *bq;
 };
-// Levels of this many children and more run a wavefront per 64 children, with
+// Levels of this many children and more run a wavefront per 32 children, with
 // the activations in registers; smaller ones split each 16 children over
 // seven wavefronts (see mlp.hip).
 constexpr long long kMlpLarge = 32768;

@@ -11,8 +11,8 @@
 // conv2's 9x9 and 6x6 of conv3's 7x7.  Every output sees the matrix
 // instructions of a child computed by itself, in the same order, on the same
 // operands, so the results are the same bits; an output that no agent square
-// meets is the background's.  For 18 children that is about 590 rows of conv1
-// instead of 7,200, 260 of conv2 instead of 1,458 and 460 of conv3 instead
+// meets is the background's.  For 18 children that is 572 rows of conv1 on average
+// instead of 7,200, 210 of conv2 instead of 1,458 and 259 of conv3 instead
 // of 882, and the layers' weights are read once per group instead of once
 // per 3 stacks.  A leaf's frame is never read, and expand.hip renders none.
 //

@@ -4,16 +4,19 @@
 // An FP32 value v scaled into FP16's range is hi + lo / 2^11, hi = fp16(v), lo =
 // fp16((v - hi) 2^11): 22 to 23 bits of the 24, and a product w x is w_hi x_hi +
 // (w_hi x_lo + w_lo x_hi) / 2^11, each exact in FP32, summed in FP32.  Left out is
-// w_lo x_lo (2^-24 of w x and less, of either sign).  The pixels of conv1 are
+// w_lo x_lo (2^-22 of w x at most, of either sign).  The pixels of conv1 are
 // whole numbers, exact in FP16: two products there.  A sum over K = 32 is one
 // v_mfma_f32_16x16x32_f16 and one rounding where v_mfma_f32_16x16x4_f32 makes
 // 32.  It rounds within, too, every 4 to 8 values, so long sums are cut: the
 // small products have sums of their own, and K runs in slices summed from zero
 // (conv2 4 steps a slice, conv3 3, fc1 14).  The sums' error then falls by more
-// than the operands' rises.  Against 64 bits, of a root's largest |Q| over 768
-// searches of A = 6, d = 3: 3.0e-7 on average and 1.6e-6 at most, where the FP32
-// instruction has 6.8e-7 and 3.5e-6 (4.5e-7 and 2.4e-6 with one sum for all
-// products and no slices in the conv layers, 3% faster).
+// than the operands' rises.  Against 64 bits, of a root's largest |Q| over 1,024
+// searches of A = 6, d = 3 with Kaiming-uniform weights: 2.9e-7 on average and
+// 2.0e-6 at most, where the FP32 instruction has 6.5e-7 and 3.4e-6 (one sum for
+// all products and no slices in the conv layers: 1.5 times the error, 3% faster).
+// Of a stack's largest |Q| over 768 stacks: heavy-tailed weights (Student's t, 4
+// degrees) 2.8e-7 and 6.0e-7, channels uneven by a normal of two bits 2.8e-7 and
+// 6.0e-7.
 //
 // Time, 256 searches of A = 6, d = 3 (57,088 stacks): conv layers 2.3 ms where
 // layer-by-layer kernels on v_mfma_f32_16x16x4_f32 took 5.86 (the FP32

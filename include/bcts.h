@@ -121,8 +121,9 @@ bcts_status bcts_reset(bcts_ctx* ctx);
 bcts_status bcts_set_env(bcts_ctx* ctx, const bcts_env_params* env);
 
 /* Q-network weights: FP32 blob of BCTS_QNET_NUMEL floats (layout above),
- * copied and converted on the device for every precision.  A search with A
- * actions uses fc2 rows 0..A-1.  Resets FP8 scales to their calibration
+ * copied and converted on the device for every precision (the FP32 copy, 7 MB,
+ * lies in pinned host memory where FP32 runs on two FP16 values, see
+ * BCTS_TUNE_FUSED).  A search with A actions uses fc2 rows 0..A-1.  Resets FP8 scales to their calibration
  * default (see bcts_calibrate_fp8).                                         */
 bcts_status bcts_set_qnet(bcts_ctx* ctx, const float* blob, size_t n_floats);
 /* Precision of the Q-network for subsequent searches (default BCTS_FP32).  */
